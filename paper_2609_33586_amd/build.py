@@ -18,7 +18,8 @@ from pathlib import Path
 
 PKG = Path(__file__).resolve().parent
 ROOT = PKG.parent
-SRC = PKG / "csrc" / "h15attn.hip"     # kernels and their launchers
+SRC = PKG / "csrc" / "h15attn.hip"     # forward kernels and their launchers
+DECODE_SRC = PKG / "csrc" / "h15decode.hip"  # decode kernels and their launchers
 API_SRC = PKG / "csrc" / "attn_api.cpp"  # C entry points: argument checks, per-call constants
 INCLUDE = ROOT / "include"
 LIB_PATH = PKG / "libh15attn.so"
@@ -37,7 +38,7 @@ def hipcc() -> str:
     return str(Path(rocm) / "bin" / "hipcc")
 
 
-# The kernel source is compiled twice: once for everything but the FP8
+# The forward kernel source is compiled twice: once for everything but the FP8
 # lattice-weight forward kernels at d = 128, once for those alone, which are
 # scheduled with the iterative ILP machine scheduler (faster for them, slower
 # for the exact control and the BF16 kernels, and at d = 64 it would cost the
@@ -45,6 +46,7 @@ def hipcc() -> str:
 UNITS = [
     ("kernels", SRC, []),
     ("fp8_lattice_d128", SRC, ["-DH15_FP8_LATTICE_D128=1", "-mllvm", "-amdgpu-sched-strategy=iterative-ilp"]),
+    ("decode", DECODE_SRC, []),
     ("api", API_SRC, []),
 ]
 

@@ -126,6 +126,16 @@ int fill_params(Params& p, const void* q, const void* k, const void* v, void* o,
 }
 
 
+// Decode grids up to this many workgroups, one per compute unit, read K
+// through LDS also at BF16 d = 128, where that leaves room for only one
+// workgroup per CU: whole-row copies feed a CU faster than operand loads (one
+// sequence, 1000 keys: 14.1 -> 12.8 us; 2 x 4 heads, 3000 keys: 18.6 -> 16.6).
+// Larger grids are bound by HBM and want two workgroups per CU (K in
+// registers against LDS: B16 8K 95.2 / 97.4 us, B64 4K 170.4 / 173.9, B200 1K
+// 146.1 / 151.0).  FP8 and d = 64 take LDS always: two workgroups fit.
+constexpr long long DEC_KLDS_GROUPS = 256;
+
+
 // Number of key parts for a cut of split_keys keys (0 or >= Sk: one part).
 int dec_parts(int Sk, int split_keys) {
   if (split_keys <= 0 || split_keys >= Sk) return 1;
@@ -207,8 +217,15 @@ int bind_workspace(DecParams& p, int d, void* workspace, size_t workspace_bytes)
   return ATTN_OK;
 }
 
-int decode_launch(const DecParams& p, int dtype, int d, int causal, int exp_mode, void* st, bool probe) {
+// Whether K goes through LDS.
+int decode_k_lds(const DecParams& p, int dtype, int d) {
+  const long long groups = (long long)p.B * p.Hkv * p.nrb * p.nsplit;
+  return (groups <= DEC_KLDS_GROUPS || dtype != ATTN_BF16 || d != 128) ? 1 : 0;
+}
+
+int decode_launch(DecParams& p, int dtype, int d, int causal, int exp_mode, void* st, bool probe) {
   const int mode = kernel_mode(dtype, exp_mode, d, p.ck);
+  p.k_lds = decode_k_lds(p, dtype, d);
   return launch_decode(p, dtype, d, causal, mode, st, probe) == 0 ? ATTN_OK : ATTN_ELAUNCH;
 }
 }  // namespace

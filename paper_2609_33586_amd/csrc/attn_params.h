@@ -60,6 +60,7 @@ struct DecParams {
   float* part_o;   // [rows][nsplit][d], unnormalised O of each part (nsplit > 1)
   float* part_ml;  // [rows][nsplit][2], (m, l) of each part (nsplit > 1)
   int B, Hq, Hkv, Sq, Sk, Sk_cap, G, R, nrb, nsplit, split_keys;
+  int k_lds;  // 1: K through LDS (0 only for BF16 at d = 128)
   float c1, ck, vd;
   // probe target (probe launches only): output row (pb, ph, pi)
   int pb, ph, pi;
@@ -68,7 +69,7 @@ struct DecParams {
   uint32_t* p_out;
 };
 
-// Launchers (h15attn.hip).  Each enqueues its kernels on stream (a
+// Launchers (h15attn.hip; launch_decode and the scratch: h15decode.hip).  Each enqueues its kernels on stream (a
 // hipStream_t; NULL: the default stream) and returns 0, or nonzero when the
 // runtime reports a launch error.  The caller has checked every argument.
 int launch_fwd(const Params& p, int dtype, int d, int causal, int mode, void* stream, bool probe);
@@ -77,7 +78,7 @@ int launch_probe_fill(float* s, float* w, uint32_t* pbits, size_t n, void* strea
 // the parts' kernel, then (several parts) their merge
 int launch_decode(const DecParams& p, int dtype, int d, int causal, int mode, void* stream, bool probe);
 
-// The library's built-in decode workspace (h15attn.hip): its size in bytes,
+// The library's built-in decode workspace (h15decode.hip): its size in bytes,
 // and the address of the current device's copy for work on stream (NULL:
 // the default stream).  Returns 0; 1 when the runtime cannot name the
 // device, the stream's device or the address; 2 when the stream belongs to

@@ -29,15 +29,7 @@
 //     weights of the other 64 are finished between them (split P), so that
 //     a wave's VALU work overlaps its own matrix-core work;
 //   * O leaves through LDS, so that each store covers whole rows.
-#include <hip/hip_runtime.h>
-#include <math.h>
-#include <stdint.h>
-
-#include <mutex>
-#include <type_traits>
-
-#include "attn_params.h"
-#include "h15attn.h"
+#include "attn_device.h"
 
 // The file is compiled twice (build.py): with H15_FP8_LATTICE_D128 = 1 it
 // holds only the forward kernels of the FP8 lattice weights at d = 128 and
@@ -57,92 +49,14 @@ namespace {
 
 using namespace h15;
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-typedef int i32x2v __attribute__((__vector_size__(2 * sizeof(int))));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef short i16x2 __attribute__((ext_vector_type(2)));
-
-#define LDS_PTR(T, p) ((__attribute__((address_space(3))) T*)(p))
-
-enum { DT_BF16 = 0, DT_FP8 = 1 };
-
-// Waves per workgroup in the default layout: 4 for FP8 (two workgroups
-// share a CU, so one's barrier and prologue stalls overlap the other's
-// work), 8 for BF16 (whose double-buffered tiles at d = 128 leave LDS for
-// only one workgroup per CU; the compact layout, Cfg below, has 4).
-template <int DT>
-constexpr int waves_per_group() {
-  return DT == DT_FP8 ? 4 : 8;
-}
 constexpr int MAX_THREADS = 8 * 64;
 // LDS operand prefetch distance (in MFMAs) of the QK^T and PV products
 constexpr int QK_AHEAD = 3;
 constexpr int PV_AHEAD = 3;
-// word 3 of a raw buffer resource on CDNA (32-bit data format, no swizzle)
-constexpr int BUF_DWORD3 = 0x00020000;
 // instruction classes of __builtin_amdgcn_sched_group_barrier
 constexpr int SG_MFMA = 0x008;
 constexpr int SG_DS_READ = 0x100;
-constexpr float H15_MAGIC = 12582912.0f;  // 0x4B400000 = 2^23 + 2^22
-// top half of bits(1.0) in both 16-bit lanes
-constexpr uint32_t ONE_BITS16X2 = 0x3F803F80u;
-
-// Kernel weight modes (attn_params.h): the order k of a lattice mode, and its
-// clamp form.
-constexpr int mode_order(int mode) { return (mode + 1) / 2; }
-constexpr bool mode_lattice(int mode) { return mode != MODE_EXACT && mode != MODE_ROWMAX_POT; }
-constexpr bool mode_narrow(int mode) { return mode_lattice(mode) && mode % 2 == 0; }
 constexpr int POT_KMAX = 20;  // tail clamp of Rowmax-PoT
-
-// CMP: the compact layout for grids that underfill the chip (BF16, chosen
-// per call on the host): 4 waves per group and at most 80 KB of LDS, so two
-// groups share a CU and one's prologue, barriers and epilogue overlap the
-// other's work; at d = 128 that means single-buffered K and V tiles.
-template <int DT, int D, bool CMP = false>
-struct Cfg {
-  static constexpr int EB = DT == DT_BF16 ? 2 : 1;  // operand bytes
-  static constexpr int RB = D * EB;                 // bytes per K/V row
-  static constexpr int NCH = RB / 16;               // 16-byte chunks per row
-  static constexpr int TILE = BC * RB;              // bytes of one K (or V) tile
-  static constexpr int BUF = 2 * TILE;              // K then V
-  static constexpr int CHUNKS = BC * NCH;           // 16-byte chunks per tile
-  static constexpr int NW = CMP ? 4 : waves_per_group<DT>();  // waves per workgroup
-  static constexpr int BR = NW * WROWS;                       // query rows per workgroup
-  // K/V tile buffers: two (the copy of tile t + 1 overlaps tile t), or one
-  // when two would not let two compact groups share a CU's 160 KB of LDS
-  static constexpr int NSTAGE = (CMP && 2 * BUF > 80 * 1024) ? 1 : 2;
-  static_assert(CHUNKS % (NW * 64) == 0, "tile/staging mismatch");
-  static_assert(BR == (CMP ? FWD_ROWS_COMPACT : DT == DT_FP8 ? FWD_ROWS_FP8 : FWD_ROWS_BF16),
-                "row block of attn_params.h");
-};
-
-// Bank-spreading XOR swizzles of the 16-byte chunks of a row.  K rows are read
-// as the MFMA A operand (one chunk of 32 consecutive rows per instruction);
-// V rows through the transposing reads (4 rows x 2 chunks for bf16, 8 rows x
-// 1 chunk for fp8 per 16 lanes).  An fp8 row is 128 bytes, half the banks'
-// width, so rows r and r + 1 start on different bank halves; the K swizzle
-// then varies with r / 2, so that 16 consecutive rows reading one logical
-// chunk cover every bank once (with r % NCH, rows r and r + 8 shared banks;
-// the counter read 2,080 conflict cycles per wave at d = 128, now zero).
-template <int DT, int D>
-__device__ __forceinline__ int k_swz(int row) {
-  using C = Cfg<DT, D>;
-  if constexpr (DT == DT_BF16) return row % C::NCH;
-  else return (row >> 1) % C::NCH;
-}
-template <int DT, int D>
-__device__ __forceinline__ int v_swz(int row) {
-  using C = Cfg<DT, D>;
-  if constexpr (DT == DT_BF16) return ((C::NCH >= 16 ? 4 : 2) * (row & 3)) % C::NCH;
-  else return ((row & 3) | (((row >> 3) & 1) << 2)) % C::NCH;
-}
 
 __device__ __forceinline__ void map_block(const Params& p, int L, int& qb, int& b, int& h) {
   const int nbh = p.B * p.Hq;
@@ -180,68 +94,8 @@ __device__ __forceinline__ void map_block(const Params& p, int L, int& qb, int& 
   }
 }
 
-// Weight of one score, S(Q_{2^-k}(x)) with k = mode_order(MODE) (App. B.1
-// "Implementation" for k = 1, App. B.2 "Exponential-map ablation" for k = 2,
-// 3): y = 2^k x = fma(s, 2^k c1, nb), clamp at -126 * 2^k, RNE add of
-// 0x4B400000 (n = RNE(y) lands in the low mantissa bits), left shift by
-// 23 - k (the low k bits of n become the top mantissa bits, the rest the
-// exponent), plus the bits of 1.0, all modulo 2^32.
-//
-// Such a weight has at most k <= 3 mantissa bits, so the low 16 bits of its
-// FP32 pattern are zero and its top 16 bits, (n << (7 - k)) + 0x3F80 modulo
-// 2^16, are its exact BF16 pattern.  The kernel finishes the weights two at
-// a time in the 16-bit lanes of one register: the row sum takes one
-// two-element dot product per pair, and the pair is already a BF16 operand
-// (or one packed conversion away from FP8).
-//
-// sq_pre: the 32-bit value whose low half carries n: bits(max(y, -126 2^k) +
-// magic), or for the narrow clamp bits(y + magic) (the magic's low half is
-// zero, so the low half is n modulo 2^16).
-template <int MODE>
-__device__ __forceinline__ uint32_t sq_pre(float s, float ck, float nbk) {
-  constexpr int K = mode_order(MODE);
-  const float y = __builtin_fmaf(s, ck, nbk);
-  if constexpr (mode_narrow(MODE)) return __float_as_uint(y + H15_MAGIC);
-  else return __float_as_uint(__builtin_fmaxf(y, -126.0f * (float)(1 << K)) + H15_MAGIC);
-}
-
-// The BF16 weights of two keys in one word (u0 in the low lane): the low
-// halves of their sq_pre values, the narrow clamp max(n, -126 2^k) on int16
-// lanes (n is then n itself: the launcher selects the narrow mode only when
-// every |y| is provably below 2^15), and n 2^(7-k) + 0x3F80 per lane modulo
-// 2^16 in one packed multiply-add.
-template <int MODE>
-__device__ __forceinline__ uint32_t sq_pack(uint32_t u0, uint32_t u1) {
-  constexpr int K = mode_order(MODE);
-  uint32_t x = __builtin_amdgcn_perm(u1, u0, 0x05040100u);
-  if constexpr (mode_narrow(MODE)) {
-    constexpr short lo = (short)(-126 * (1 << K));
-    x = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, x), i16x2{lo, lo}));
-  }
-  // the multiplier is an inline constant read from its low half in both
-  // lanes (op_sel_hi 0); the addend comes from a scalar register
-  uint32_t r;
-  asm("v_pk_mad_u16 %0, %1, %2, %3 op_sel_hi:[1,0,1]" : "=v"(r) : "v"(x), "n"(1 << (7 - K)), "s"(ONE_BITS16X2));
-  return r;
-}
-
-// sq_pre value of a masked key: its packed weight is +0.  n = 385 * 2^k gives
-// n 2^(7-k) = 0xC080 = -0x3F80 modulo 2^16, and lies above the narrow clamp.
-template <int MODE>
-constexpr uint32_t sq_masked() {
-  return 385u << mode_order(MODE);
-}
-// (0x4B3F0000 | sq_masked) = 0x1.8p23 - 2^16 + sq_masked lies below
-// 0x1.8p23 - 2^15 for every mode
-static_assert((385u << 3) < (1u << 15), "the lift stays below every narrow-mode t");
-
 // init plus the row sum of a tile's packed weights: one dot product with
 // (1, 1) per word, in two chains.
-__device__ __forceinline__ float dot2_ones(uint32_t w, float acc) {
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), ones, acc, false);
-}
-
 __device__ __forceinline__ float pair_sum(const uint32_t (&w)[4][8], float init) {
   const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
   float a[2] = {init, 0.0f};
@@ -262,20 +116,6 @@ __device__ __forceinline__ float pot_weight(float s, float m, float c1) {
   return __builtin_amdgcn_ldexpf(1.0f, -(int)d);
 }
 
-// x, or y where key offset C lies beyond this lane's last valid offset lim.
-// Compare and select go through VCC together (C as an immediate): written
-// as plain C the compiler keeps all 64 masks of a tile live in scalar
-// registers at once.
-template <int C>
-__device__ __forceinline__ float select_beyond(int lim, float x, float y) {
-  float r;
-  // volatile: keeps the masking inside the branch that needs it
-  asm volatile("v_cmp_gt_i32 vcc, %1, %2\n\tv_cndmask_b32 %0, %3, %4, vcc"
-               : "=v"(r)
-               : "n"(C), "v"(lim), "v"(x), "v"(y)
-               : "vcc");
-  return r;
-}
 // y over the scores of a tile whose key offset lies beyond lim
 template <int E = 0>
 __device__ __forceinline__ void mask_beyond(f32x16 (&v)[4], int lim, float y) {
@@ -284,49 +124,6 @@ __device__ __forceinline__ void mask_beyond(f32x16 (&v)[4], int lim, float y) {
     v[kb][j] = select_beyond<kb * 32 + 8 * (j >> 2) + (j & 3)>(lim, v[kb][j], y);
     mask_beyond<E + 1>(v, lim, y);
   }
-}
-
-// This lane's value and that of lane i ^ 32 (in an order that depends on the
-// lane), exchanged on the VALU rather than through LDS.
-__device__ __forceinline__ void with_partner(float x, float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  a = __uint_as_float(r[0]);
-  b = __uint_as_float(r[1]);
-}
-
-// Compile-time loop: f(integral_constant<int, I>) for I in [B, E).
-template <int B, int E, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (B < E) {
-    f(std::integral_constant<int, B>{});
-    static_for<B + 1, E>(f);
-  }
-}
-
-// Transposing LDS reads written as inline asm.  The compiler's wait counting
-// would make the intrinsic forms wait for every LDS copy in flight (it cannot
-// tell that those copies land in other buffers); here the caller waits for
-// the reads itself with lds_wait, which also orders the uses after the wait.
-template <int OFF>
-__device__ __forceinline__ i32x2v ds_read_tr8(uint32_t addr) {
-  static_assert(OFF >= 0 && OFF < 65536, "ds offset");
-  i32x2v r;
-  asm volatile("ds_read_b64_tr_b8 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF));
-  return r;
-}
-template <int OFF>
-__device__ __forceinline__ i32x2v ds_read_tr16(uint32_t addr) {
-  static_assert(OFF >= 0 && OFF < 65536, "ds offset");
-  i32x2v r;
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF));
-  return r;
-}
-// Wait until at most N LDS operations of this wave are outstanding (they
-// complete in order), then hand x on as produced after the wait.
-template <int N, typename T>
-__device__ __forceinline__ void lds_wait(T& x) {
-  static_assert(N >= 0 && N < 16, "lgkmcnt range");
-  asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));
 }
 
 // The scores of a tile are next read by inline asm (the v_max3_f32 tree of
@@ -342,15 +139,8 @@ __device__ __forceinline__ void settle_scores(f32x16 (&v)[4]) {
   asm("s_nop 15\n\ts_nop 7" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
 }
 
-// Tree reductions over a lane's 64 scores (short dependency chains).  The
-// maximum is taken with v_max3_f32 directly: fmaxf on matrix-core results
-// would first canonicalize every input (one extra instruction per score).
-// Its reads of the scores come after settle_scores.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
+// Tree reductions over a lane's 64 scores (short dependency chains); the
+// reads of the scores come after settle_scores.
 __device__ __forceinline__ float tile_max(const f32x16 (&v)[4]) {
   // 64 -> 22 -> 8 -> 3 -> 1
   float a[22], b[8], c[3];
@@ -1186,588 +976,6 @@ hipError_t launch_any(const Params& p, int dtype, int d, int causal, int mode, h
                   : launch_dt_d<DT_FP8, 64, PROBE>(p, causal, mode, st);
 }
 
-// ---------------------------------------------------------------------------
-// Decode over a key/value cache: Sq query rows per head against Sk cached
-// keys (bottom-right causal alignment), the keys cut into parts of
-// split_keys keys that workgroups take in parallel.  Within a part the
-// per-tile recurrence runs as in the forward kernel, with tiles starting at
-// the part's first key and the running maximum starting at -inf; the parts'
-// (m, l, O) then merge exactly (attn_decode_merge).  One part: the kernel
-// normalises and writes O and LSE itself.
-//
-// One workgroup = 4 waves for one (batch, KV head, block of 32 query rows,
-// part).  The 32 rows are the G * Sq query rows of the KV head's query heads
-// (row r: head h = hkv G + r / Sq, position r % Sq), so the K/V tiles are read
-// once for all of them.  Wave w computes the scores of keys 32w .. 32w + 31
-// of each 128-key tile (one 32x32 block of S^T = K Q^T) and their share of
-// PV; the tile maximum of each row is combined across the four waves through
-// LDS, so every wave moves the same running maximum at every tile, and the
-// waves' partial row sums and O accumulators, all relative to that maximum,
-// are added up at the end.
-//
-// Decode reads the cache once and is bound by HBM, so the copies are laid
-// out to keep as many bytes in flight as LDS allows: each wave loads only
-// its own 32 keys, K straight into its MFMA operand registers (one tile
-// ahead) and V into its own LDS slots (DEC_VSTAGES slots, so V of the next
-// DEC_VSTAGES - 1 tiles is in flight); no barrier is needed for the copies,
-// only the one per tile for the row maxima.  66 KB of LDS per group and at
-// most 256 VGPRs per lane, so two groups share a CU (measured: with four
-// times the V slots and one group per CU the per-tile chain of a lone wave
-// per SIMD left FP8 decode 50% slower; with two groups FP8 +3% and BF16
-// +11% against copies shared through double-buffered tiles).
-
-constexpr int DEC_NW = 4;  // waves per decode workgroup (one 32-key block each)
-template <int DT>
-constexpr int dec_vstages() {
-  return DT == DT_FP8 ? 4 : 2;
-}
-
-// s_waitcnt for vmcnt <= N only (gfx9 encoding: vmcnt in bits 3:0 and 15:14;
-// expcnt 6:4 and lgkmcnt 11:8 at their maxima, so not waited for)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
-__device__ __forceinline__ void settle_block(f32x16& v) {
-  // as settle_scores, for one block
-  asm("s_nop 15\n\ts_nop 7" : "+v"(v));
-}
-
-template <int E = 0>
-__device__ __forceinline__ void mask_beyond1(f32x16& v, int lim, float y) {
-  if constexpr (E < 16) {
-    v[E] = select_beyond<8 * (E >> 2) + (E & 3)>(lim, v[E], y);
-    mask_beyond1<E + 1>(v, lim, y);
-  }
-}
-
-__device__ __forceinline__ float block_max(const f32x16& v) {
-  // 16 -> 6 -> 2 -> 1
-  const float a0 = max3(v[0], v[1], v[2]), a1 = max3(v[3], v[4], v[5]), a2 = max3(v[6], v[7], v[8]);
-  const float a3 = max3(v[9], v[10], v[11]), a4 = max3(v[12], v[13], v[14]);
-  const float b0 = max3(a0, a1, a2), b1 = max3(a3, a4, v[15]);
-  return max3(b0, b1, b1);
-}
-
-template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
-__global__ __launch_bounds__(DEC_NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_kernel(
-    DecParams p) {
-  using C = Cfg<DT, D>;
-  constexpr int NW = DEC_NW;
-  constexpr int NSV = dec_vstages<DT>();
-  constexpr int VSLOT = WROWS * C::RB;  // one wave's 32 V rows of a tile
-  constexpr int NDB = D / 32;
-  constexpr int NKQ = DT == DT_BF16 ? D / 16 : D / 64;
-  constexpr int VLOADS = VSLOT / 1024;                   // 1 KB LDS copies per wave and tile
-  constexpr int KLOADS = DT == DT_BF16 ? NKQ : 2 * NKQ;  // 16-byte K loads per lane and tile
-  // loads issued after V(t) by the time tile t reads it, once every step
-  // issues its K and V copies
-  constexpr int VWAIT = (NSV - 1) * (KLOADS + VLOADS);
-  static_assert(VSLOT % 1024 == 0 && (NSV & (NSV - 1)) == 0, "V slots");
-  static_assert(NW * NDB * 16 * 64 * 4 <= NW * NSV * VSLOT, "the O reduction reuses the V slots");
-  __shared__ __attribute__((aligned(16))) uint8_t smem[NW * NSV * VSLOT];
-  __shared__ __attribute__((aligned(16))) float mx_lds[2][32][NW];
-  __shared__ float l_lds[NW][64];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int i32 = lane & 31;
-  const int g = lane >> 5;
-  const int G4 = lane >> 4, L16 = lane & 15;
-
-  int L = blockIdx.x;
-  const int split = L % p.nsplit;
-  L /= p.nsplit;
-  const int rb = L % p.nrb;
-  const int bkv = L / p.nrb;
-  const int b = bkv / p.Hkv, hkv = bkv - b * p.Hkv;
-  const int row = rb * WROWS + i32;
-  const bool row_ok = row < p.R;
-  const int rowc = min(row, p.R - 1);
-  const int gq = rowc / p.Sq, iq = rowc - gq * p.Sq;
-  const int h = hkv * p.G + gq;
-  const size_t orow = (size_t)(b * p.Hq + h) * (size_t)p.Sq + (size_t)iq;
-  const int Sk = p.Sk;
-  const int limit = CAUSAL ? Sk - p.Sq + iq : Sk - 1;  // last key this row sees
-  const int j0 = split * p.split_keys;
-  const int j1 = min(j0 + p.split_keys, Sk);
-  const int ntiles = (j1 - j0 + BC - 1) / BC;
-  const float off = DT == DT_FP8 ? 8.0f : 0.0f;
-
-  // ---- Q rows (MFMA B operand: lane holds row i32, k-half g)
-  const uint8_t* qptr = p.q + orow * C::RB;
-  bf16x8 qb16[DT == DT_BF16 ? NKQ : 1];
-  i32x8 qf8[DT == DT_FP8 ? NKQ : 1];
-  if constexpr (DT == DT_BF16) {
-#pragma unroll
-    for (int kk = 0; kk < NKQ; ++kk) qb16[kk] = *(const bf16x8*)(qptr + (16 * kk + 8 * g) * 2);
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < NKQ; ++kk) qf8[kk] = *(const i32x8*)(qptr + 64 * kk + 32 * g);
-  }
-
-  // ---- the part's K and V rows through buffer resources that start at the
-  // part's first key and end at the cache length, so rows at or beyond Sk
-  // read as zero (those keys are masked)
-  const uint8_t* kg = p.k + ((size_t)bkv * (size_t)p.Sk_cap + (size_t)j0) * C::RB;
-  const uint8_t* vg = p.v + ((size_t)bkv * (size_t)p.Sk_cap + (size_t)j0) * C::RB;
-  const __amdgpu_buffer_rsrc_t krsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void*)kg, (short)0, (Sk - j0) * C::RB, BUF_DWORD3);
-  const __amdgpu_buffer_rsrc_t vrsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void*)vg, (short)0, (Sk - j0) * C::RB, BUF_DWORD3);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-
-  // K of this wave's 32 keys of tile t straight into the MFMA A operand
-  // (lane: key 32 wave + i32; bf16: 16 bytes at 32 kk + 16 g of the row;
-  // fp8: 32 bytes at 64 kk + 32 g)
-  using KOp = std::conditional_t<DT == DT_BF16, bf16x8, i32x8>;
-  const uint32_t krow = (uint32_t)((32 * wave + i32) * C::RB);
-  auto load_k = [&](int t, KOp (&dst)[NKQ]) __attribute__((always_inline)) {
-    const int soff = t * BC * C::RB;
-#pragma unroll
-    for (int kk = 0; kk < NKQ; ++kk) {
-      if constexpr (DT == DT_BF16) {
-        dst[kk] = __builtin_bit_cast(
-            bf16x8, __builtin_amdgcn_raw_buffer_load_b128(krsrc, (int)(krow + 32 * kk + 16 * g), soff, 0));
-      } else {
-        const i32x4 lo = __builtin_bit_cast(
-            i32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, (int)(krow + 64 * kk + 32 * g), soff, 0));
-        const i32x4 hi = __builtin_bit_cast(
-            i32x4, __builtin_amdgcn_raw_buffer_load_b128(krsrc, (int)(krow + 64 * kk + 32 * g + 16), soff, 0));
-        dst[kk] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-    }
-  };
-  // V of this wave's 32 keys of tile t into its LDS slot t % NSV: slot byte
-  // s holds row s / RB with the forward kernel's chunk swizzle (the swizzle
-  // depends on the row modulo 16, which the 32-row offset keeps)
-  uint32_t voff_c[VLOADS];
-#pragma unroll
-  for (int c = 0; c < VLOADS; ++c) {
-    const int slot = c * 64 + lane;
-    const int r = slot / C::NCH, pch = slot % C::NCH;
-    voff_c[c] = (uint32_t)(r * C::RB + ((pch ^ v_swz<DT, D>(r)) << 4));
-  }
-  auto vslot = [&](int t) { return smem + ((t & (NSV - 1)) * NW + wave_s) * VSLOT; };
-  auto stage_v = [&](int t) __attribute__((always_inline)) {
-    const uint32_t soff = (uint32_t)((t * BC + 32 * wave_s) * C::RB);
-    uint8_t* const base = vslot(t);
-#pragma unroll
-    for (int c = 0; c < VLOADS; ++c) {
-      const uint32_t voff = voff_c[c];
-      uint8_t* ldst = base + c * 1024;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(vrsrc, LDS_PTR(void, ldst), 16, voff, soff, 0, 0);
-    }
-  };
-
-  // ---- V^T operand addresses (as the forward kernel's, within this wave's
-  // slot of 32 rows)
-  uint32_t vbase[NDB];
-  auto set_vbase = [&](const uint8_t* vl) __attribute__((always_inline)) {
-    const uint32_t vla = (uint32_t)(size_t)LDS_PTR(const uint8_t, vl);
-    if constexpr (DT == DT_BF16) {
-      const int vrow = 4 * (G4 >> 1) + (L16 >> 2);
-      const int vcolb = (16 * (G4 & 1) + 4 * (L16 & 3)) * 2;
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        const int cb = 64 * db + vcolb;
-        vbase[db] = vla + vrow * C::RB + (((cb >> 4) ^ v_swz<DT, D>(vrow)) << 4) + (cb & 15);
-      }
-    } else {
-      const int vrow = 4 * (G4 >> 1) + 8 * (L16 >> 3) + ((L16 >> 1) & 3);
-      const int vcol = 16 * (G4 & 1) + 8 * (L16 & 1);
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        const int cb = 32 * db + vcol;
-        vbase[db] = vla + vrow * C::RB + (((cb >> 4) ^ v_swz<DT, D>(vrow)) << 4) + (cb & 15);
-      }
-    }
-  };
-
-  f32x16 oacc[NDB];
-#pragma unroll
-  for (int db = 0; db < NDB; ++db) oacc[db] = f32x16{0.0f};
-  float m_run = -INFINITY;
-  float l_part = 0.0f;
-  const bool probe_row = PROBE && row_ok && b == p.pb && h == p.ph && iq == p.pi;
-
-  // K(0) and V(0 .. NSV - 2) first; step t then issues K(t + 1) and
-  // V(t + NSV - 1), in that order, before its own work
-  KOp kreg[2][NKQ];
-  load_k(0, kreg[0]);
-  for (int s = 0; s < NSV - 1; ++s)
-    if (s < ntiles) stage_v(s);
-  auto step = [&](int t, KOp (&kc)[NKQ], KOp (&kn)[NKQ]) __attribute__((always_inline)) {
-    if (t + 1 < ntiles) load_k(t + 1, kn);
-    if (t + NSV - 1 < ntiles) stage_v(t + NSV - 1);
-    const int kt0 = j0 + t * BC;    // first key of the tile
-    const int kw0 = kt0 + 32 * wave;  // first key of this wave's block
-
-    // ---- S^T block of this wave's 32 keys
-    f32x16 sv;
-    if constexpr (DT == DT_BF16) {
-#pragma unroll
-      for (int kk = 0; kk < NKQ; ++kk)
-        sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kc[kk], qb16[kk], kk == 0 ? f32x16{0.0f} : sv, 0, 0, 0);
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < NKQ; ++kk)
-        sv = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(kc[kk], qf8[kk], kk == 0 ? f32x16{0.0f} : sv, 0, 0, 0,
-                                                             0, 0, 0);
-    }
-    settle_block(sv);
-
-    // ---- masking: keys beyond the row's limit or the cache
-    const bool need_mask = (CAUSAL && kt0 + BC - 1 > Sk - p.Sq) || (kt0 + BC > Sk);
-    const int lim = limit - kw0 - 4 * g;
-    if (need_mask) mask_beyond1(sv, lim, -INFINITY);
-    if constexpr (PROBE) {
-      if (probe_row) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int key = kw0 + 8 * (j >> 2) + 4 * g + (j & 3);
-          if (key < Sk) p.s_out[key] = sv[j];
-        }
-      }
-    }
-
-    // ---- the tile maximum of each row, over the four waves' blocks
-    {
-      float ma, mb;
-      with_partner(block_max(sv), ma, mb);
-      if (g == 0) mx_lds[t & 1][i32][wave] = __builtin_fmaxf(ma, mb);
-    }
-    // (the two copies of mx_lds alternate, so a wave that runs ahead writes
-    // the other one: every wave has read this one before the next barrier)
-    __syncthreads();
-    const f32x4 mx4 = *(const f32x4*)&mx_lds[t & 1][i32][0];
-    const float m_new = max3(m_run, __builtin_fmaxf(mx4[0], mx4[1]), __builtin_fmaxf(mx4[2], mx4[3]));
-    // a row that has seen no key yet keeps m = -inf, l = 0, O = 0
-    const float alpha = m_new == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c1);
-    const float m_use = m_new == -INFINITY ? 0.0f : m_new;
-    m_run = m_new;
-
-    // ---- weights (in place), row sum, P
-    uint32_t wpk[8];
-    constexpr bool PACKED = mode_lattice(MODE);
-    if constexpr (PACKED) {
-      const float nbk = __builtin_fmaf(-m_use, p.ck, (float)(1 << mode_order(MODE)) * off);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sv[j] = __uint_as_float(sq_pre<MODE>(sv[j], p.ck, nbk));
-      if (need_mask) {
-        if constexpr (mode_narrow(MODE)) {
-          const float lift = __uint_as_float(0x4B3F0000u | sq_masked<MODE>());
-#pragma unroll
-          for (int j = 0; j < 16; ++j) sv[j] = max3(sv[j], lift, lift);
-        } else {
-          mask_beyond1(sv, lim, __uint_as_float(sq_masked<MODE>()));
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) wpk[q] = sq_pack<MODE>(__float_as_uint(sv[2 * q]), __float_as_uint(sv[2 * q + 1]));
-      float a0 = l_part * alpha, a1 = 0.0f;
-#pragma unroll
-      for (int q = 0; q < 8; q += 2) {
-        a0 = dot2_ones(wpk[q], a0);
-        a1 = dot2_ones(wpk[q + 1], a1);
-      }
-      l_part = a0 + a1;
-    } else {
-      const float nb1 = __builtin_fmaf(-m_use, p.c1, off);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) sv[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[j], p.c1, nb1));
-      float a[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) a[i] = sv[i] + sv[i + 8];
-#pragma unroll
-      for (int w = 4; w >= 1; w >>= 1)
-#pragma unroll
-        for (int i = 0; i < w; ++i) a[i] = a[i] + a[i + w];
-      l_part = l_part * alpha + a[0];
-    }
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-      for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
-    }
-
-    // P in the operand type: bf16 as two 16-key operands; fp8 as one 64-key
-    // operand whose other 32 keys (another wave's) carry P = 0
-    bf16x8 pb2[2];
-    i32x8 pf;
-    if constexpr (DT == DT_BF16) {
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        if constexpr (PACKED) {
-          pb2[ks] = __builtin_bit_cast(bf16x8, u32x4{wpk[4 * ks], wpk[4 * ks + 1], wpk[4 * ks + 2], wpk[4 * ks + 3]});
-        } else {
-#pragma unroll
-          for (int r = 0; r < 8; ++r) pb2[ks][r] = (__bf16)sv[8 * ks + r];
-        }
-      }
-    } else {
-      int pw[4];
-#pragma unroll
-      for (int w4 = 0; w4 < 4; ++w4) {
-        if constexpr (PACKED) {
-          i16x2 word = __builtin_bit_cast(i16x2, wpk[2 * w4]);
-          word = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(word, __builtin_bit_cast(bf16x2, wpk[2 * w4]), 1.0f, false);
-          word = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(word, __builtin_bit_cast(bf16x2, wpk[2 * w4 + 1]), 1.0f,
-                                                           true);
-          pw[w4] = __builtin_bit_cast(int, word);
-        } else {
-          uint32_t word = __float_as_uint(sv[4 * w4]);
-          word = __builtin_amdgcn_cvt_pk_fp8_f32(sv[4 * w4], sv[4 * w4 + 1], word, false);
-          word = __builtin_amdgcn_cvt_pk_fp8_f32(sv[4 * w4 + 2], sv[4 * w4 + 3], word, true);
-          pw[w4] = (int)word;
-        }
-      }
-      if (wave & 1) pf = i32x8{0, 0, 0, 0, pw[0], pw[1], pw[2], pw[3]};
-      else pf = i32x8{pw[0], pw[1], pw[2], pw[3], 0, 0, 0, 0};
-    }
-    if constexpr (PROBE) {
-      if (probe_row) {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int key = kw0 + 8 * (j >> 2) + 4 * g + (j & 3);
-          if (key < Sk && key <= limit) {
-            uint32_t bits;
-            if constexpr (DT == DT_BF16) {
-              const u32x4 pw4 = __builtin_bit_cast(u32x4, pb2[j >> 3]);
-              bits = (pw4[(j & 7) >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-            } else {
-              bits = ((uint32_t)pf[4 * (wave & 1) + (j >> 2)] >> (8 * (j & 3))) & 0xFFu;
-            }
-            p.w_out[key] = mode_lattice(MODE) ? __uint_as_float(((wpk[j >> 1] >> (16 * (j & 1))) & 0xFFFFu) << 16)
-                                              : sv[j];
-            p.p_out[key] = bits;
-          }
-        }
-      }
-    }
-
-    // ---- O^T += V^T P^T over this wave's keys, from its slot of V(t): this
-    // wave's copy of V(t) has landed once at most VWAIT later loads are
-    // outstanding (when every step so far issued its copies), or none is.
-    // (The probe's stores also count as outstanding memory operations, so
-    // the probe waits for all.)
-    if (!PROBE && t >= NSV - 1 && t + NSV - 1 < ntiles) wait_vmcnt<VWAIT>();
-    else wait_vmcnt<0>();
-    set_vbase(vslot(t));
-    if constexpr (DT == DT_BF16) {
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        i32x2v r0 = ds_read_tr16<0>(vbase[db]);
-        i32x2v r1 = ds_read_tr16<8 * C::RB>(vbase[db]);
-        i32x2v r2 = ds_read_tr16<16 * C::RB>(vbase[db]);
-        i32x2v r3 = ds_read_tr16<24 * C::RB>(vbase[db]);
-        lds_wait<0>(r0);
-        lds_wait<0>(r1);
-        lds_wait<0>(r2);
-        lds_wait<0>(r3);
-        const bf16x8 v0 = __builtin_bit_cast(bf16x8, __builtin_shufflevector(r0, r1, 0, 1, 2, 3));
-        const bf16x8 v1 = __builtin_bit_cast(bf16x8, __builtin_shufflevector(r2, r3, 0, 1, 2, 3));
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v0, pb2[0], oacc[db], 0, 0, 0);
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v1, pb2[1], oacc[db], 0, 0, 0);
-      }
-    } else {
-      const i32x2v zero2 = {0, 0};
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        i32x2v r0 = ds_read_tr8<0>(vbase[db]);
-        i32x2v r1 = ds_read_tr8<16 * C::RB>(vbase[db]);
-        lds_wait<0>(r0);
-        lds_wait<0>(r1);
-        const i32x4 mine = __builtin_shufflevector(r0, r1, 0, 1, 2, 3);
-        const i32x4 none = __builtin_shufflevector(zero2, zero2, 0, 1, 2, 3);
-        const i32x8 vop = (wave & 1) ? __builtin_shufflevector(none, mine, 0, 1, 2, 3, 4, 5, 6, 7)
-                                     : __builtin_shufflevector(mine, none, 0, 1, 2, 3, 4, 5, 6, 7);
-        oacc[db] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vop, pf, oacc[db], 0, 0, 0, 0, 0, 0);
-      }
-    }
-  };
-  // tiles in pairs, so that each step's K registers are fixed at compile time
-  for (int t = 0; t < ntiles; t += 2) {
-    step(t, kreg[0], kreg[1]);
-    if (t + 1 < ntiles) step(t + 1, kreg[1], kreg[0]);
-  }
-  // every copy has landed and every wave is done with its V slots before the
-  // slots are reused for the reduction
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-
-  // ---- the four waves' partial sums: O^T blocks and row sums through LDS
-  {
-    float la, lb;
-    with_partner(l_part, la, lb);
-    l_lds[wave][lane] = la + lb;
-    float* red = (float*)smem;  // [wave][db][j][lane]
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) red[((wave * NDB + db) * 16 + j) * 64 + lane] = oacc[db][j];
-  }
-  __syncthreads();
-  if (!row_ok) return;
-  const float l = (l_lds[0][lane] + l_lds[1][lane]) + (l_lds[2][lane] + l_lds[3][lane]);
-  if (wave < NDB) {
-    const int db = wave;
-    const float* red = (const float*)smem;
-    f32x16 osum;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) acc += red[((w * NDB + db) * 16 + j) * 64 + lane];
-      osum[j] = acc;
-    }
-    if (p.nsplit == 1) {
-      const float inv = p.vd / l;
-      uint16_t* orp = p.o + orow * (size_t)D;
-#pragma unroll
-      for (int jq = 0; jq < 4; ++jq) {
-        const int col = 32 * db + 8 * jq + 4 * g;
-        const __bf16 a0 = (__bf16)(osum[4 * jq + 0] * inv);
-        const __bf16 a1 = (__bf16)(osum[4 * jq + 1] * inv);
-        const __bf16 a2 = (__bf16)(osum[4 * jq + 2] * inv);
-        const __bf16 a3 = (__bf16)(osum[4 * jq + 3] * inv);
-        const uint32_t w01 = (uint32_t)__builtin_bit_cast(uint16_t, a0) |
-                             ((uint32_t)__builtin_bit_cast(uint16_t, a1) << 16);
-        const uint32_t w23 = (uint32_t)__builtin_bit_cast(uint16_t, a2) |
-                             ((uint32_t)__builtin_bit_cast(uint16_t, a3) << 16);
-        *(u32x2*)(orp + col) = u32x2{w01, w23};
-      }
-    } else {
-      float* pop = p.part_o + (orow * (size_t)p.nsplit + (size_t)split) * (size_t)D;
-#pragma unroll
-      for (int jq = 0; jq < 4; ++jq) {
-        const int col = 32 * db + 8 * jq + 4 * g;
-        *(f32x4*)(pop + col) = f32x4{osum[4 * jq], osum[4 * jq + 1], osum[4 * jq + 2], osum[4 * jq + 3]};
-      }
-    }
-  }
-  if (wave == 0 && g == 0) {
-    if (p.nsplit == 1) {
-      if (p.lse) p.lse[orow] = 0.69314718055994531f * (m_run * p.c1 + log2f(l) - off);
-    } else {
-      *(f32x2*)(p.part_ml + (orow * (size_t)p.nsplit + (size_t)split) * 2) = f32x2{m_run, l};
-    }
-  }
-}
-
-struct MergeParams {
-  const float* part_o;
-  const float* part_ml;
-  uint16_t* o;
-  float* lse;
-  int rows, nsplit;
-  float c1, vd, off;
-};
-
-// The parts of each output row merged exactly: m = max m_p, f_p =
-// 2^(c1 (m_p - m)) (0 for a part that saw no key), l = sum f_p l_p,
-// O = sum f_p O_p / l * v_descale, LSE = ln2 (m c1 + log2 l - off).  One wave
-// per row; lane j holds elements j * D / 64 .. of the row.
-template <int D>
-__global__ __launch_bounds__(256) void attn_decode_merge(MergeParams p) {
-  constexpr int E = D / 64;
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= p.rows) return;
-  const float* ml = p.part_ml + (size_t)row * p.nsplit * 2;
-  float m = -INFINITY;
-  for (int s = 0; s < p.nsplit; ++s) m = __builtin_fmaxf(m, ml[2 * s]);
-  float l = 0.0f;
-  float acc[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.0f;
-  const float* po = p.part_o + (size_t)row * p.nsplit * D + lane * E;
-  for (int s = 0; s < p.nsplit; ++s) {
-    const float ms = ml[2 * s];
-    const float f = ms == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((ms - m) * p.c1);
-    l += f * ml[2 * s + 1];
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] += f * po[(size_t)s * D + e];
-  }
-  const float inv = p.vd / l;
-  uint16_t* orp = p.o + (size_t)row * D + lane * E;
-#pragma unroll
-  for (int e = 0; e < E; ++e) orp[e] = __builtin_bit_cast(uint16_t, (__bf16)(acc[e] * inv));
-  if (p.lse && lane == 0) p.lse[row] = 0.69314718055994531f * (m * p.c1 + log2f(l) - p.off);
-}
-
-template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
-hipError_t launch_dec_one(const DecParams& p, hipStream_t st) {
-  const unsigned grid = (unsigned)(p.B * p.Hkv * p.nrb * p.nsplit);
-  hipLaunchKernelGGL((attn_decode_kernel<DT, D, CAUSAL, MODE, PROBE>), dim3(grid), dim3(DEC_NW * 64), 0, st, p);
-  return hipGetLastError();
-}
-
-template <int DT, int D, bool CAUSAL, bool PROBE>
-hipError_t launch_dec_mode(const DecParams& p, int mode, hipStream_t st) {
-  switch (mode) {
-    case MODE_EXACT: return launch_dec_one<DT, D, CAUSAL, MODE_EXACT, PROBE>(p, st);
-    case 1: return launch_dec_one<DT, D, CAUSAL, 1, PROBE>(p, st);
-    case 3: return launch_dec_one<DT, D, CAUSAL, 3, PROBE>(p, st);
-    case 5: return launch_dec_one<DT, D, CAUSAL, 5, PROBE>(p, st);
-    default: break;
-  }
-  if constexpr (DT == DT_FP8) {
-    switch (mode) {
-      case 2: return launch_dec_one<DT, D, CAUSAL, 2, PROBE>(p, st);
-      case 4: return launch_dec_one<DT, D, CAUSAL, 4, PROBE>(p, st);
-      case 6: return launch_dec_one<DT, D, CAUSAL, 6, PROBE>(p, st);
-      default: break;
-    }
-  }
-  return hipErrorInvalidValue;
-}
-
-template <bool PROBE>
-hipError_t launch_dec_any(const DecParams& p, int dtype, int d, int causal, int mode, hipStream_t st) {
-  if (dtype == ATTN_BF16) {
-    if (d == 128)
-      return causal ? launch_dec_mode<DT_BF16, 128, true, PROBE>(p, mode, st)
-                    : launch_dec_mode<DT_BF16, 128, false, PROBE>(p, mode, st);
-    return causal ? launch_dec_mode<DT_BF16, 64, true, PROBE>(p, mode, st)
-                  : launch_dec_mode<DT_BF16, 64, false, PROBE>(p, mode, st);
-  }
-  if (d == 128)
-    return causal ? launch_dec_mode<DT_FP8, 128, true, PROBE>(p, mode, st)
-                  : launch_dec_mode<DT_FP8, 128, false, PROBE>(p, mode, st);
-  return causal ? launch_dec_mode<DT_FP8, 64, true, PROBE>(p, mode, st)
-                : launch_dec_mode<DT_FP8, 64, false, PROBE>(p, mode, st);
-}
-
-hipError_t launch_merge(const DecParams& dp, int dtype, int d, hipStream_t st) {
-  MergeParams mp;
-  mp.part_o = dp.part_o;
-  mp.part_ml = dp.part_ml;
-  mp.o = dp.o;
-  mp.lse = dp.lse;
-  mp.rows = dp.B * dp.Hq * dp.Sq;
-  mp.nsplit = dp.nsplit;
-  mp.c1 = dp.c1;
-  mp.vd = dp.vd;
-  mp.off = dtype == ATTN_FP8_E4M3 ? 8.0f : 0.0f;
-  const unsigned grid = (unsigned)((mp.rows + 3) / 4);
-  if (d == 128) hipLaunchKernelGGL(attn_decode_merge<128>, dim3(grid), dim3(256), 0, st, mp);
-  else hipLaunchKernelGGL(attn_decode_merge<64>, dim3(grid), dim3(256), 0, st, mp);
-  return hipGetLastError();
-}
-
-// Built-in workspace of attn_decode_noalloc: the parts' (m, l, O) of one
-// decode call, for callers that cannot allocate.  Each GPU the library runs
-// on holds its own copy until the process ends.  In host code the name is
-// only a stand-in for the device address: the address each device uses is
-// looked up once per device (scratch_address) and only that is passed on.
-constexpr size_t SCRATCH_BYTES = (size_t)16 << 20;
-static __device__ __align__(256) uint8_t scratch[SCRATCH_BYTES];
-
 #endif  // !H15_FP8_LATTICE_D128
 
 }  // namespace
@@ -1780,32 +988,6 @@ hipError_t launch_fwd_fp8_lattice128(const Params& p, bool causal, int mode, hip
   return causal ? launch_lattice128<true, false>(p, mode, st) : launch_lattice128<false, false>(p, mode, st);
 }
 #else
-size_t scratch_capacity() { return SCRATCH_BYTES; }
-
-int scratch_address(void* stream, void** ptr) {
-  constexpr int MAX_DEVICES = 64;
-  static std::mutex mu;
-  static void* addr[MAX_DEVICES] = {};
-  int dev = -1;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return 1;
-  if (stream) {
-    // the kernels run on the stream's device: its buffer is the one to use,
-    // and it is looked up with the current device, so the two must agree
-    hipDevice_t sdev = -1;
-    if (hipStreamGetDevice((hipStream_t)stream, &sdev) != hipSuccess) return 1;
-    if (sdev != dev) return 2;
-  }
-  std::lock_guard<std::mutex> lock(mu);
-  if (!addr[dev]) {
-    // with the device current: this device's copy of the array
-    void* a = nullptr;
-    if (hipGetSymbolAddress(&a, HIP_SYMBOL(scratch)) != hipSuccess || !a) return 1;
-    addr[dev] = a;
-  }
-  *ptr = addr[dev];
-  return 0;
-}
-
 int launch_fwd(const Params& p, int dtype, int d, int causal, int mode, void* stream, bool probe) {
   hipStream_t st = (hipStream_t)stream;
   const hipError_t e = probe ? launch_any<true>(p, dtype, d, causal, mode, st)
@@ -1817,14 +999,6 @@ int launch_probe_fill(float* s, float* w, uint32_t* pbits, size_t n, void* strea
   hipLaunchKernelGGL(probe_fill, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream, s, w, pbits,
                      n);
   return hipGetLastError() == hipSuccess ? 0 : 1;
-}
-
-int launch_decode(const DecParams& p, int dtype, int d, int causal, int mode, void* stream, bool probe) {
-  hipStream_t st = (hipStream_t)stream;
-  hipError_t e = probe ? launch_dec_any<true>(p, dtype, d, causal, mode, st)
-                       : launch_dec_any<false>(p, dtype, d, causal, mode, st);
-  if (e == hipSuccess && p.nsplit > 1) e = launch_merge(p, dtype, d, st);
-  return e == hipSuccess ? 0 : 1;
 }
 #endif
 
