@@ -52,23 +52,43 @@ int kernel_mode(int dtype, int exp_mode, int d, float ck) {
 constexpr int COMPACT_MAX_S = 2048;
 constexpr long long COMPACT_BELOW_GROUPS = 512;
 
-// 1 when the forward call takes the compact layout: BF16 (FP8 groups are 4
-// waves already) and any weight but Rowmax-PoT (whose first pass
-// double-buffers K).
-int use_compact(int dtype, int exp_mode, int B, int Hq, int S) {
-  if (dtype != ATTN_BF16 || exp_mode == ATTN_EXP_ROWMAX_POT) return 0;
-  const long long groups = (long long)B * Hq * ((S + FWD_ROWS_BF16 - 1) / FWD_ROWS_BF16);
-  return (S <= COMPACT_MAX_S || groups < COMPACT_BELOW_GROUPS) ? 1 : 0;
+// The paired layout (8 waves for 128 rows, two waves a row) where there are
+// not enough blocks of 128 rows for two on every one of the 256 compute
+// units, so that a wave would have its SIMD to itself: up to 256 blocks, from
+// five key tiles on (causal: four), below which its exchange at the end costs
+// what the shorter chain of tiles gains; and causal up to 512 blocks of long
+// rows, where the longest blocks decide when the call ends.  Paired against
+// the other layouts, time ratio at d = 128 (FP8 / BF16, causal unless said):
+// 128 blocks of 512 keys 1.05 / 1.12, 1K 1.10 / 1.19, 4K 1.19 / 1.29, all keys
+// visible 512 keys 1.02 / 1.08, 4K 1.19 / 1.30; 512 blocks of 1K keys 0.92 /
+// 0.96, 2K 1.05 / 1.05, 4K 1.12 / 1.13; 288 blocks of 512 keys 0.90 / 0.97, 2K
+// 1.16 / 1.11; 256 blocks of 256 keys 0.99 / 1.01; 288 blocks with all keys
+// visible 0.73; 600 blocks of 4K 0.91 / 0.88.
+bool use_paired(long long blocks, int S, int causal) {
+  const int tiles = (S + BC - 1) / BC;
+  if (blocks <= 256) return tiles >= (causal ? 4 : 5);
+  return causal && blocks <= 512 && S >= 4 * blocks;
+}
+
+// The layout of a forward call (attn_device.h); Rowmax-PoT, whose first pass
+// double-buffers K, always takes the wide one.
+int fwd_layout(int dtype, int exp_mode, int B, int Hq, int S, int causal) {
+  if (exp_mode == ATTN_EXP_ROWMAX_POT) return LAY_WIDE;
+  const long long heads = (long long)B * Hq;
+  if (use_paired(heads * ((S + FWD_ROWS_SMALL - 1) / FWD_ROWS_SMALL), S, causal)) return LAY_PAIRED;
+  if (dtype != ATTN_BF16) return LAY_WIDE;
+  const long long groups = heads * ((S + FWD_ROWS_BF16 - 1) / FWD_ROWS_BF16);
+  return (S <= COMPACT_MAX_S || groups < COMPACT_BELOW_GROUPS) ? LAY_COMPACT : LAY_WIDE;
 }
 
 // query rows per workgroup for an operand type and layout
-int row_block(int dtype, int compact) {
-  if (compact) return FWD_ROWS_COMPACT;
+int row_block(int dtype, int layout) {
+  if (layout != LAY_WIDE) return FWD_ROWS_SMALL;
   return dtype == ATTN_FP8_E4M3 ? FWD_ROWS_FP8 : FWD_ROWS_BF16;
 }
 
 int fill_params(Params& p, const void* q, const void* k, const void* v, void* o, float* lse, int B,
-                int Hq, int Hkv, int S, int d, float scale, int dtype, int exp_mode,
+                int Hq, int Hkv, int S, int d, int causal, float scale, int dtype, int exp_mode,
                 const attn_opts* opts) {
   if (!q || !k || !v || !o) return ATTN_EINVAL;
   if (B <= 0 || Hq <= 0 || Hkv <= 0 || S <= 0 || d <= 0) return ATTN_EINVAL;
@@ -119,8 +139,8 @@ int fill_params(Params& p, const void* q, const void* k, const void* v, void* o,
   p.vd = vd;
   p.tau = tau;
   p.tau_wave = (opts && opts->rescale_per_wave) ? 1 : 0;
-  p.compact = use_compact(dtype, exp_mode, B, Hq, S);
-  p.nqb = (S + row_block(dtype, p.compact) - 1) / row_block(dtype, p.compact);
+  p.layout = fwd_layout(dtype, exp_mode, B, Hq, S, causal);
+  p.nqb = (S + row_block(dtype, p.layout) - 1) / row_block(dtype, p.layout);
   p.remap = ((B * Hkv) % 8 == 0) ? 1 : 0;
   return ATTN_OK;
 }
@@ -249,7 +269,7 @@ int attn_fwd_ex(const void* q, const void* k, const void* v, void* o, float* lse
                 int Hkv, int S, int d, int causal, float scale, int dtype, int exp_mode,
                 const attn_opts* opts) {
   Params p;
-  const int rc = fill_params(p, q, k, v, o, lse, B, Hq, Hkv, S, d, scale, dtype, exp_mode, opts);
+  const int rc = fill_params(p, q, k, v, o, lse, B, Hq, Hkv, S, d, causal, scale, dtype, exp_mode, opts);
   if (rc != ATTN_OK) return rc;
   if (p.remap && !causal) p.remap = 2;
   void* st = opts ? opts->stream : nullptr;
@@ -269,7 +289,7 @@ int attn_fwd_probe(const void* q, const void* k, const void* v, void* o, float* 
                    const attn_opts* opts, int b, int h, int row0, int nrows, float* s_out,
                    float* w_out, uint32_t* p_bits_out) {
   Params p;
-  const int rc = fill_params(p, q, k, v, o, lse, B, Hq, Hkv, S, d, scale, dtype, exp_mode, opts);
+  const int rc = fill_params(p, q, k, v, o, lse, B, Hq, Hkv, S, d, causal, scale, dtype, exp_mode, opts);
   if (rc != ATTN_OK) return rc;
   if (p.remap && !causal) p.remap = 2;
   if (!s_out || !w_out || !p_bits_out) return ATTN_EINVAL;

@@ -54,11 +54,16 @@ constexpr int mode_order(int mode) { return (mode + 1) / 2; }
 constexpr bool mode_lattice(int mode) { return mode != MODE_EXACT && mode != MODE_ROWMAX_POT; }
 constexpr bool mode_narrow(int mode) { return mode_lattice(mode) && mode % 2 == 0; }
 
-// CMP: the compact layout for grids that underfill the chip (BF16, chosen
-// per call on the host): 4 waves per group and at most 80 KB of LDS, so two
-// groups share a CU and one's prologue, barriers and epilogue overlap the
-// other's work; at d = 128 that means single-buffered K and V tiles.
-template <int DT, int D, bool CMP = false>
+// Layouts of a forward workgroup (which one a call takes is decided on the
+// host, attn_api.cpp):
+//   LAY_WIDE    waves_per_group waves of 32 query rows each, one key tile a step;
+//   LAY_COMPACT BF16: 4 waves and at most 80 KB of LDS, so two groups share a
+//               CU and one's prologue, barriers and epilogue overlap the
+//               other's work; at d = 128 that means single-buffered tiles;
+//   LAY_PAIRED  8 waves for 128 query rows: waves w and w + 4 have the same
+//               rows and take the even and the odd key tiles, half a step
+//               apart, each four with single-buffered tiles of their own.
+template <int DT, int D, int LAY = LAY_WIDE>
 struct Cfg {
   static constexpr int EB = DT == DT_BF16 ? 2 : 1;  // operand bytes
   static constexpr int RB = D * EB;                 // bytes per K/V row
@@ -66,13 +71,15 @@ struct Cfg {
   static constexpr int TILE = BC * RB;              // bytes of one K (or V) tile
   static constexpr int BUF = 2 * TILE;              // K then V
   static constexpr int CHUNKS = BC * NCH;           // 16-byte chunks per tile
-  static constexpr int NW = CMP ? 4 : waves_per_group<DT>();  // waves per workgroup
-  static constexpr int BR = NW * WROWS;                       // query rows per workgroup
+  static constexpr int NW = LAY == LAY_COMPACT ? 4 : LAY == LAY_PAIRED ? 8 : waves_per_group<DT>();  // waves per group
+  static constexpr int NPAR = LAY == LAY_PAIRED ? 2 : 1;  // waves with the same rows
+  static constexpr int RW = NW / NPAR;                    // waves that share a tile
+  static constexpr int BR = RW * WROWS;                   // query rows per workgroup
   // K/V tile buffers: two (the copy of tile t + 1 overlaps tile t), or one
   // when two would not let two compact groups share a CU's 160 KB of LDS
-  static constexpr int NSTAGE = (CMP && 2 * BUF > 80 * 1024) ? 1 : 2;
-  static_assert(CHUNKS % (NW * 64) == 0, "tile/staging mismatch");
-  static_assert(BR == (CMP ? FWD_ROWS_COMPACT : DT == DT_FP8 ? FWD_ROWS_FP8 : FWD_ROWS_BF16),
+  static constexpr int NSTAGE = LAY == LAY_PAIRED || (LAY == LAY_COMPACT && 2 * BUF > 80 * 1024) ? 1 : 2;
+  static_assert(CHUNKS % (RW * 64) == 0, "tile/staging mismatch");
+  static_assert(BR == (LAY != LAY_WIDE ? FWD_ROWS_SMALL : DT == DT_FP8 ? FWD_ROWS_FP8 : FWD_ROWS_BF16),
                 "row block of attn_params.h");
 };
 
@@ -213,6 +220,15 @@ template <int N, typename T>
 __device__ __forceinline__ void lds_wait(T& x) {
   static_assert(N >= 0 && N < 16, "lgkmcnt range");
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));
+}
+
+// Barrier that makes this workgroup's LDS writes visible and leaves loads
+// from memory in flight (fences, also those of LDS alone, wait for the copies
+// into LDS).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // v_max3_f32 directly: fmaxf on matrix-core results would first canonicalize

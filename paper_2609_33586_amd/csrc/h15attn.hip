@@ -4,8 +4,9 @@
 // (App. B.2), or Rowmax-PoT (App. A.6), behind the C ABI declared in
 // h15attn.h.
 //
-// Kernel structure (one workgroup = 4 wave64s for FP8, 8 or 4 for BF16; 32 query
-// rows of one head per wave; two waves per SIMD, three for FP8 at d = 64):
+// Kernel structure (one workgroup = 4 wave64s for FP8, 8 or 4 for BF16, 32 query
+// rows of one head per wave; or, where the grid leaves compute units idle, 8
+// waves for 128 rows; two waves per SIMD, three for FP8 at d = 64):
 //   * each wave keeps its 32 query rows of Q in VGPRs as the MFMA B operand,
 //     brought in through LDS with whole-row loads;
 //   * key tiles of 128 keys are copied HBM -> LDS with buffer loads that
@@ -14,6 +15,11 @@
 //     tile) or single-buffered (K(t+1) copied while the weights and PV of
 //     tile t run, V(t+1) while QK^T of tile t+1 runs, two barriers per tile:
 //     the lattice weights at FP8 d = 128, and the compact BF16 layout);
+//   * in the paired layout the even and the odd tiles of a block of rows go
+//     to two halves of the workgroup, each single-buffered on its own, one
+//     barrier apart; the two waves of a row exchange tile maxima, so that every
+//     tile's anchor is the running maximum in tile order, and add up their
+//     sums at the end;
 //   * scores are computed transposed, S^T = K Q^T, with 32x32 MFMAs (bf16
 //     32x32x16, fp8 32x32x64): each lane owns one query row and 64 of the
 //     tile's 128 keys, so the row max and row sum are in-lane reductions plus
@@ -169,22 +175,26 @@ __device__ __forceinline__ float tile_sum(const f32x16 (&v)[4]) {
   return a[0];
 }
 
-// Two waves per SIMD, three for fp8 at d = 64 (163 VGPRs, 32 KB of LDS per
-// workgroup: three workgroups fit a CU, and the third wave hides more of the
-// VALU latency in that VALU-bound case).
-template <int DT, int D, bool CAUSAL, int MODE, bool PROBE, bool CMP>
-__global__ __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(2, (DT == DT_FP8 && D == 64) ? 3 : 2))) void
-attn_fwd_kernel(Params p) {
-  using C = Cfg<DT, D, CMP>;
-  constexpr int NW = C::NW, BR = C::BR;
+template <int DT, int D, bool CAUSAL, int MODE, bool PROBE, int LAY>
+__device__ __forceinline__ void fwd_body(const Params& p) {
+  using C = Cfg<DT, D, LAY>;
+  constexpr int NW = C::NW, BR = C::BR, RW = C::RW;
+  constexpr bool PAIR = LAY == LAY_PAIRED;
   // K and V tiles, each double-buffered, or single-buffered: compact d = 128,
   // and the lattice weights at FP8 d = 128 (measured at causal and
   // non-causal 8K: H15 +1.7..2.4% single-buffered, the exact control
   // -0.7%, so the control keeps two buffers)
-  constexpr int NSTAGE = (DT == DT_FP8 && D == 128 && mode_lattice(MODE)) ? 1 : C::NSTAGE;
-  static_assert(NSTAGE == 2 || MODE != MODE_ROWMAX_POT, "the Rowmax-PoT first pass double-buffers K");
-  __shared__ __attribute__((aligned(16))) uint8_t smem[NSTAGE * C::BUF];
-
+  constexpr int NSTAGE = (LAY == LAY_WIDE && DT == DT_FP8 && D == 128 && mode_lattice(MODE)) ? 1 : C::NSTAGE;
+  static_assert(MODE != MODE_ROWMAX_POT || (NSTAGE == 2 && !PAIR), "the Rowmax-PoT first pass double-buffers K");
+  // paired: the tiles of each half of the waves; at the end the fp32 halves of
+  // O that the pairs exchange, then the bf16 rows
+  constexpr int NOB = D / 32 / C::NPAR;  // 32-column blocks of O that a wave writes
+  constexpr int OX = PAIR ? NW * NOB * 4096 : 0, OST = NW * WROWS * NOB * 64;
+  constexpr int TILES = C::NPAR * NSTAGE * C::BUF;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[TILES > OX + OST ? TILES : OX + OST];
+  // paired: each row's maximum in the last two tiles of either half; at the
+  // end the waves' anchors and row sums
+  __shared__ float mx_lds[2][2][PAIR ? BR : 1];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -197,7 +207,11 @@ attn_fwd_kernel(Params p) {
   const int S = p.S;
   const int hk = h / p.G;
   const int q0 = qb * BR;
-  const int qw0 = q0 + wave * WROWS;
+  // row wave; paired: parity of this wave's tiles
+  const int rw = __builtin_amdgcn_readfirstlane(wave % RW);
+  const int par = PAIR ? __builtin_amdgcn_readfirstlane(wave / RW) : 0;
+  uint8_t* const tiles = smem + par * C::BUF;
+  const int qw0 = q0 + rw * WROWS;
   const int qrow = qw0 + i32;
   const bool wave_live = qw0 < S;
   const int last_key = CAUSAL ? min(q0 + BR - 1, S - 1) : S - 1;
@@ -223,9 +237,8 @@ attn_fwd_kernel(Params p) {
   // uses K buffer t % 2 and V buffer t % 2.
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kg, (short)0, S * C::RB, BUF_DWORD3);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)vg, (short)0, S * C::RB, BUF_DWORD3);
-  auto kbuf = [&](int t) { return smem + (t & 1) * C::BUF; };
-  auto vbuf = [&](int t) { return smem + (t & 1) * C::BUF + C::TILE; };
-  // Every wave copies its WAVE_LOADS 1 KB blocks of a tile.  The lane's byte
+  auto kbuf = [&](int t) { return tiles + (t & 1) * C::BUF; };
+  // Each of the waves that share a tile copies its WAVE_LOADS 1 KB blocks.  The lane's byte
   // offset inside the tile is the same for every tile, so it is computed
   // once; a tile then adds only the scalar offset of its first row.  Rows at
   // or beyond S (the ragged last tile) lie outside the resource's
@@ -236,29 +249,23 @@ attn_fwd_kernel(Params p) {
   // (The addresses handed to the LDS-copy builtin are named variables: with
   // an arithmetic expression in those arguments the host side of this
   // compiler drops the kernels' launch stubs without a diagnostic.)
-  constexpr int WAVE_LOADS = C::CHUNKS / (NW * 64);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  uint32_t koff_c[WAVE_LOADS], voff_c[WAVE_LOADS];
-#pragma unroll
-  for (int c = 0; c < WAVE_LOADS; ++c) {
-    const int slot = (c * NW + wave) * 64 + lane;
-    const int row = slot / C::NCH, pch = slot % C::NCH;
-    koff_c[c] = (uint32_t)(row * C::RB + ((pch ^ k_swz<DT, D>(row)) << 4));
-    voff_c[c] = (uint32_t)(row * C::RB + ((pch ^ v_swz<DT, D>(row)) << 4));
-  }
-  auto stage = [&](int t, uint8_t* dst, const __amdgpu_buffer_rsrc_t& rsrc,
-                   const uint32_t (&off_c)[WAVE_LOADS]) __attribute__((always_inline)) {
+  constexpr int WAVE_LOADS = C::CHUNKS / (RW * 64);
+  const int wave_s = __builtin_amdgcn_readfirstlane(rw);
+  // the chunk swizzles repeat every 16 rows, and a workgroup's 1 KB blocks
+  // advance by a multiple of that, so one lane offset serves all loads
+  static_assert(RW * 64 / C::NCH % 16 == 0, "the swizzle repeats from load to load");
+  const int srow = (rw * 64 + lane) / C::NCH, spch = lane % C::NCH;
+  const uint32_t koff = (uint32_t)(srow * C::RB + ((spch ^ k_swz<DT, D>(srow)) << 4));
+  const uint32_t voff = (uint32_t)(srow * C::RB + ((spch ^ v_swz<DT, D>(srow)) << 4));
+  auto stage = [&](int t, uint8_t* dst, const __amdgpu_buffer_rsrc_t& rsrc, uint32_t off) __attribute__((always_inline)) {
     const uint32_t soff = (uint32_t)(t * BC) * C::RB;
 #pragma unroll
     for (int c = 0; c < WAVE_LOADS; ++c) {
-      const uint32_t voff = off_c[c];
-      uint8_t* ldst = dst + (c * NW + wave_s) * 1024;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(void, ldst), 16, voff, soff, 0, 0);
+      const uint32_t so = soff + c * RW * 1024;
+      uint8_t* ldst = dst + (c * RW + wave_s) * 1024;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(void, ldst), 16, off, so, 0, 0);
     }
   };
-  auto stage_k = [&](int t) { stage(t, kbuf(t), krsrc, koff_c); };
-  auto stage_v = [&](int t) { stage(t, vbuf(t), vrsrc, voff_c); };
-
   // ---- Q through LDS: each wave copies its own 32 rows with the same
   // direct loads (16 contiguous bytes per lane, so each load covers whole
   // rows; rows at or beyond S read as zero), into a region the first K/V
@@ -269,11 +276,12 @@ attn_fwd_kernel(Params p) {
   // barrier after read_q).
   constexpr int QBYTES = WROWS * C::RB;
   constexpr int QREGION = NSTAGE == 1 ? C::TILE : C::BUF;
-  static_assert(QBYTES % 1024 == 0 && QREGION + NW * QBYTES <= NSTAGE * C::BUF, "Q staging layout");
+  static_assert(QBYTES % 1024 == 0 && QREGION + RW * QBYTES <= NSTAGE * C::BUF, "Q staging layout");
   const __amdgpu_buffer_rsrc_t qrsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)(p.q + q_head * C::RB), (short)0, S * C::RB, BUF_DWORD3);
   uint8_t* const qreg = smem + QREGION + wave_s * QBYTES;
   auto stage_q = [&]() __attribute__((always_inline)) {
+    if (par != 0) return;  // the other wave of the pair copies them
 #pragma unroll
     for (int c = 0; c < QBYTES / 1024; ++c) {
       const int slot = c * 64 + lane;
@@ -307,6 +315,7 @@ attn_fwd_kernel(Params p) {
 #pragma unroll
   for (int db = 0; db < NDB; ++db) oacc[db] = f32x16{0.0f};
   float m_run = -INFINITY;
+  float m_tile = -INFINITY;  // paired: the row's maximum in the open tile
   float l_part = 0.0f;  // this lane's share of the row sum
   // scores, then weights, of the current tile; accumulator value j of block
   // kb holds key 32 kb + 8 (j/4) + 4 g + j%4 of the tile
@@ -564,45 +573,57 @@ attn_fwd_kernel(Params p) {
     }
   };
 
-  // ---- the scores of tile t become weights, the running state moves, and P
-  // is left in pb/pf for the PV product
-  auto softmax_tile = [&](int t, const uint8_t* vl) __attribute__((always_inline)) {
-    const int kt0 = t * BC;
-
-    // masking: causal diagonal and the ragged tail only
+  // ---- masking (causal diagonal and the ragged tail only), and the probe's
+  // scores; returns whether the tile needed masking
+  auto finish_scores = [&](int t) __attribute__((always_inline)) {
     const bool need_mask = mask_scores(t);
-
-    const bool probe_row = PROBE && b == p.pb && h == p.ph && qrow >= p.prow0 && qrow < p.prow0 + p.pnrows;
     if constexpr (PROBE) {
-      if (probe_row) {
+      if (b == p.pb && h == p.ph && qrow >= p.prow0 && qrow < p.prow0 + p.pnrows) {
         const size_t rbase = (size_t)(qrow - p.prow0) * S;
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
-            const int key = kt0 + kb * 32 + 8 * (j >> 2) + 4 * g + (j & 3);
+            const int key = t * BC + kb * 32 + 8 * (j >> 2) + 4 * g + (j & 3);
             if (key < S) p.s_out[rbase + key] = sacc[kb][j];
           }
       }
     }
+    return need_mask;
+  };
+
+  // ---- the anchor after a tile whose row maximum is the larger of ma and mb
+  auto next_anchor = [&](float m, float ma, float mb) __attribute__((always_inline)) {
+    float m_new = max3(m, ma, mb);
+    if (DT == DT_BF16 && p.tau > 0.0f) {
+      // conditional rescale (App. B.2; FP8 requires tau = 0): the anchor
+      // moves only when the row's maximum grows by more than tau octaves
+      // (FP32 test); per wave, when any real row of the wave does
+      const float grow_by = (__builtin_fmaxf(ma, mb) - m) * p.c1;
+      bool move = m == -INFINITY || grow_by > p.tau;
+      if (p.tau_wave) move = __builtin_amdgcn_ballot_w64(move && qrow < S) != 0;
+      if (!move) m_new = m;
+    }
+    return m_new;
+  };
+
+  // ---- the scores of tile t become weights, the running state moves, and P
+  // is left in pb/pf for the PV product
+  auto softmax_tile = [&](int t, const uint8_t* vl, bool need_mask) __attribute__((always_inline)) {
+    const int kt0 = t * BC;
 
     // running maximum (threshold 0: moves to the maximum so far); Rowmax-PoT
     // keeps the whole-row maximum of its first pass
     float m_new = m_run;
-    if constexpr (MODE != MODE_ROWMAX_POT) {
-      const float mt = tile_max(sacc);
+    if constexpr (PAIR) {
+      // the tile before, which the other wave of the pair has, then this one
+      const float mp = t > 0 ? mx_lds[1 - par][((t - 1) >> 1) & 1][rw * WROWS + i32] : -INFINITY;
+      m_new = next_anchor(m_run, mp, mp);
+      m_new = next_anchor(m_new, m_tile, m_tile);
+    } else if constexpr (MODE != MODE_ROWMAX_POT) {
       float ma, mb;
-      with_partner(mt, ma, mb);
-      m_new = max3(m_run, ma, mb);
-      if (DT == DT_BF16 && p.tau > 0.0f) {
-        // conditional rescale (App. B.2; FP8 requires tau = 0): the anchor
-        // moves only when the row's maximum grows by more than tau octaves
-        // (FP32 test); per wave, when any real row of the wave does
-        const float grow_by = (__builtin_fmaxf(ma, mb) - m_run) * p.c1;
-        bool move = m_run == -INFINITY || grow_by > p.tau;
-        if (p.tau_wave) move = __builtin_amdgcn_ballot_w64(move && qrow < S) != 0;
-        if (!move) m_new = m_run;
-      }
+      with_partner(tile_max(sacc), ma, mb);
+      m_new = next_anchor(m_run, ma, mb);
     }
     const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * p.c1);
     m_run = m_new;
@@ -732,13 +753,13 @@ attn_fwd_kernel(Params p) {
     // ---- Rowmax-PoT anchors every weight at the whole-row maximum: a first
     // pass over the key tiles computes it (QK^T and the masked row max only)
     stage_q();
-    stage_k(0);
+    stage(0, kbuf(0), krsrc, koff);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     read_q();
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
-      if (t + 1 < ntiles) stage_k(t + 1);
+      if (t + 1 < ntiles) stage(t + 1, kbuf(t + 1), krsrc, koff);
       if (t <= last_act) {
         __builtin_amdgcn_s_setprio(1);
         qk(kbuf(t));
@@ -758,70 +779,91 @@ attn_fwd_kernel(Params p) {
   // ---- one tile per step: copy in the next tile, then QK^T, weights, PV.
   // Steps come in pairs so that each one's LDS buffers are fixed at compile
   // time and their addresses fold into the reads' immediate offsets.
-  // Single-buffered tiles (compact d = 128): K(t + 1) is copied in once every
-  // wave has read K(t), during the weights and PV of tile t, and V(t + 1)
-  // once every wave has read V(t), during QK^T of tile t + 1; each wait for a
-  // copy comes just before the barrier that makes it visible.
+  // Single-buffered tiles: the next K is copied in once every wave has read
+  // K, during the weights and PV, and the next V once every wave has read V,
+  // during the next QK^T; each wait for a copy comes just before the barrier
+  // that makes it visible.
+  // Paired: the waves of the odd tiles run one barrier behind those of the
+  // even ones, so of the two waves of a SIMD one is in its QK^T while the
+  // other computes weights and PV, and each tile's maximum is there when the
+  // next tile's anchor needs it.
+  auto scores = [&](const uint8_t* kl) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
+    qk(kl);
+    __builtin_amdgcn_s_setprio(0);
+    settle_scores(sacc);
+  };
+  auto weights_pv = [&](int t, const uint8_t* vl, bool need_mask) __attribute__((always_inline)) {
+    softmax_tile(t, vl, need_mask);
+    __builtin_amdgcn_s_setprio(1);
+    pv_finish();
+    __builtin_amdgcn_s_setprio(0);
+    if constexpr (SPLIT) probe_weights(t);
+  };
   auto step_single = [&](int t) __attribute__((always_inline)) {
-    uint8_t* const kl = smem;
-    uint8_t* const vl = smem + C::TILE;
+    uint8_t* const kl = tiles;
+    bool need_mask = false;
+    if constexpr (PAIR) m_tile = -INFINITY;
     if (t <= last_act) {
-      __builtin_amdgcn_s_setprio(1);
-      qk(kl);
-      __builtin_amdgcn_s_setprio(0);
-      settle_scores(sacc);
+      scores(kl);
+      if constexpr (PAIR) {
+        need_mask = finish_scores(t);
+        float ma, mb;
+        with_partner(tile_max(sacc), ma, mb);
+        m_tile = __builtin_fmaxf(ma, mb);
+      }
+    }
+    if constexpr (PAIR) {
+      if (g == 0) mx_lds[par][(t >> 1) & 1][rw * WROWS + i32] = m_tile;
     }
     // this wave's copy of V(t) has landed and its reads of K(t) are done
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (t + 1 < ntiles) stage(t + 1, kl, krsrc, koff_c);
+    if (t + C::NPAR < ntiles) stage(t + C::NPAR, kl, krsrc, koff);
     if (t <= last_act) {
-      softmax_tile(t, vl);
-      __builtin_amdgcn_s_setprio(1);
-      pv_finish();
-      __builtin_amdgcn_s_setprio(0);
-      if constexpr (SPLIT) probe_weights(t);
+      if constexpr (!PAIR) need_mask = finish_scores(t);
+      weights_pv(t, kl + C::TILE, need_mask);
     }
-    // this wave's copy of K(t + 1) has landed and its reads of V(t) are done
+    // this wave's copy of the next K has landed and its reads of V(t) are done
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (t + 1 < ntiles) stage(t + 1, vl, vrsrc, voff_c);
+    if (t + C::NPAR < ntiles) stage(t + C::NPAR, kl + C::TILE, vrsrc, voff);
   };
-  auto step = [&](int t, auto par) __attribute__((always_inline)) {
-    constexpr int P = decltype(par)::value;
+  auto step = [&](int t, auto buf) __attribute__((always_inline)) {
+    constexpr int P = decltype(buf)::value;
     uint8_t* const kl = smem + P * C::BUF;
-    uint8_t* const vl = kl + C::TILE;
     if (t + 1 < ntiles) {
-      stage(t + 1, smem + (1 - P) * C::BUF, krsrc, koff_c);
-      stage(t + 1, smem + (1 - P) * C::BUF + C::TILE, vrsrc, voff_c);
+      stage(t + 1, smem + (1 - P) * C::BUF, krsrc, koff);
+      stage(t + 1, smem + (1 - P) * C::BUF + C::TILE, vrsrc, voff);
     }
     if (t <= last_act) {
-      __builtin_amdgcn_s_setprio(1);
-      qk(kl);
-      __builtin_amdgcn_s_setprio(0);
-      settle_scores(sacc);
-      softmax_tile(t, vl);
-      __builtin_amdgcn_s_setprio(1);
-      pv_finish();
-      __builtin_amdgcn_s_setprio(0);
-      if constexpr (SPLIT) probe_weights(t);
+      scores(kl);
+      const bool need_mask = finish_scores(t);
+      weights_pv(t, kl + C::TILE, need_mask);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   };
   if constexpr (NSTAGE == 1) {
     stage_q();
-    stage(0, smem, krsrc, koff_c);
+    if (par < ntiles) stage(par, tiles, krsrc, koff);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     read_q();
     __syncthreads();
-    stage(0, smem + C::TILE, vrsrc, voff_c);
-    for (int t = 0; t < ntiles; ++t) step_single(t);
+    if (par < ntiles) stage(par, tiles + C::TILE, vrsrc, voff);
+    if constexpr (PAIR) {
+      // both halves cross the same number of barriers
+      if (par != 0) lds_barrier();
+      for (int t = par; t < (ntiles + 1) / 2 * 2; t += 2) step_single(t);
+      if (par == 0) lds_barrier();
+    } else {
+      for (int t = 0; t < ntiles; ++t) step_single(t);
+    }
   } else {
     if constexpr (MODE != MODE_ROWMAX_POT) stage_q();
-    stage_k(0);
-    stage_v(0);
+    stage(0, smem, krsrc, koff);
+    stage(0, smem + C::TILE, vrsrc, voff);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if constexpr (MODE != MODE_ROWMAX_POT) {
@@ -834,24 +876,69 @@ attn_fwd_kernel(Params p) {
     }
   }
 
-  // ---- epilogue: O = acc / l * v_descale (bf16), LSE
-  if (!wave_live) return;
+  // ---- epilogue: O = acc / l * v_descale (bf16), LSE.  A wave writes blocks
+  // DB0 .. DB0 + NOB - 1 of its rows' columns (paired: one half each).
   float la, lb;
   with_partner(l_part, la, lb);
-  const float l = la + lb;
+  float l = la + lb, m_end = m_run;
+  uint8_t* ost = smem + wave * (WROWS * NOB * 64);
+  if constexpr (PAIR) {
+    // the two waves of a pair hold sums relative to their own anchors: each
+    // sends the other its part of the other's columns through LDS, which is
+    // free once every wave has passed the last barrier
+    f32x4* const ex = (f32x4*)smem;  // [wave][block][quarter][lane]
+    auto send = [&](auto other) __attribute__((always_inline)) {
+#pragma unroll
+      for (int o = 0; o < NOB; ++o)
+#pragma unroll
+        for (int jq = 0; jq < 4; ++jq) {
+          const f32x16& a = oacc[decltype(other)::value * NOB + o];
+          ex[((wave * NOB + o) * 4 + jq) * 64 + lane] = f32x4{a[4 * jq], a[4 * jq + 1], a[4 * jq + 2], a[4 * jq + 3]};
+        }
+    };
+    if (par == 0) send(std::integral_constant<int, 1>{});
+    else send(std::integral_constant<int, 0>{});
+    if (g == 0) {
+      mx_lds[0][par][rw * WROWS + i32] = m_run;
+      mx_lds[1][par][rw * WROWS + i32] = l;
+    }
+    __syncthreads();
+    if (!wave_live) return;
+    const float m_other = mx_lds[0][1 - par][rw * WROWS + i32];
+    m_end = __builtin_fmaxf(m_run, m_other);
+    // (a wave without a visible key has m = -inf, l = 0, O = 0)
+    const float fm = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_end) * p.c1);
+    const float fo = m_other == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_other - m_end) * p.c1);
+    l = fm * l + fo * mx_lds[1][1 - par][rw * WROWS + i32];
+    const int partner = wave ^ RW;
+    auto merge = [&](auto mine) __attribute__((always_inline)) {
+#pragma unroll
+      for (int o = 0; o < NOB; ++o)
+#pragma unroll
+        for (int jq = 0; jq < 4; ++jq) {
+          const f32x4 x = ex[((partner * NOB + o) * 4 + jq) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            oacc[o][4 * jq + e] = fm * oacc[decltype(mine)::value * NOB + o][4 * jq + e] + fo * x[e];
+        }
+    };
+    if (par == 0) merge(std::integral_constant<int, 0>{});
+    else merge(std::integral_constant<int, 1>{});
+    ost += OX;
+  } else {
+    if (!wave_live) return;
+  }
   const float inv = p.vd / l;
   // O leaves through LDS, which is free once every wave has passed the last
   // barrier: the lanes write their four-column pieces into the wave's own
-  // 32 x D block (16-byte chunks XOR-swizzled by row: the reads are free of
-  // bank conflicts, the writes of rows r and r + 16 share banks) and read
-  // back 16 contiguous bytes of a row, so that each global store covers
-  // whole rows instead of 8 bytes in each of 32 rows
-  constexpr int ORB = D * 2, ONC = ORB / 16;  // bytes and 16-byte chunks per O row
-  static_assert(NW * WROWS * ORB <= NSTAGE * C::BUF, "O staging fits the tile buffers");
-  uint8_t* const ost = smem + wave * (WROWS * ORB);
-  auto oswz = [](int row) { return D == 128 ? (row & 15) : ((row >> 1) & 7); };
+  // 32-row block there (16-byte chunks XOR-swizzled by row: the reads are
+  // free of bank conflicts, the writes of rows r and r + 16 share banks) and
+  // read back 16 contiguous bytes of a row, so that each global store covers
+  // whole rows (paired: whole halves) instead of 8 bytes in each of 32 rows
+  constexpr int ORB = NOB * 64, ONC = ORB / 16;  // bytes and 16-byte chunks per staged row
+  auto oswz = [](int row) { return ONC == 16 ? (row & 15) : ONC == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); };
 #pragma unroll
-  for (int db = 0; db < NDB; ++db)
+  for (int db = 0; db < NOB; ++db)
 #pragma unroll
     for (int jq = 0; jq < 4; ++jq) {
       const __bf16 a0 = (__bf16)(oacc[db][4 * jq + 0] * inv);
@@ -871,7 +958,7 @@ attn_fwd_kernel(Params p) {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   constexpr int RPI = 64 / ONC;  // rows per store
   const int rsub = lane / ONC, csub = lane % ONC;
-  uint8_t* const obase = (uint8_t*)p.o + (q_head + qw0) * (size_t)ORB + csub * 16;
+  uint8_t* const obase = (uint8_t*)p.o + (q_head + qw0) * (size_t)(D * 2) + par * ORB + csub * 16;
   u32x4 orows[WROWS / RPI];
 #pragma unroll
   for (int k = 0; k < WROWS / RPI; ++k) {
@@ -880,14 +967,33 @@ attn_fwd_kernel(Params p) {
   }
   if (qw0 + WROWS <= S) {
 #pragma unroll
-    for (int k = 0; k < WROWS / RPI; ++k) *(u32x4*)(obase + (size_t)(RPI * k + rsub) * ORB) = orows[k];
+    for (int k = 0; k < WROWS / RPI; ++k) *(u32x4*)(obase + (size_t)(RPI * k + rsub) * (D * 2)) = orows[k];
   } else {
 #pragma unroll
     for (int k = 0; k < WROWS / RPI; ++k)
-      if (qw0 + RPI * k + rsub < S) *(u32x4*)(obase + (size_t)(RPI * k + rsub) * ORB) = orows[k];
+      if (qw0 + RPI * k + rsub < S) *(u32x4*)(obase + (size_t)(RPI * k + rsub) * (D * 2)) = orows[k];
   }
-  if (p.lse && g == 0 && qrow < S)
-    p.lse[q_head + qrow] = 0.69314718055994531f * (m_run * p.c1 + log2f(l) - off);
+  if (p.lse && par == 0 && g == 0 && qrow < S)
+    p.lse[q_head + qrow] = 0.69314718055994531f * (m_end * p.c1 + log2f(l) - off);
+}
+
+// Two waves per SIMD, three for fp8 at d = 64 (163 VGPRs, 32 KB of LDS per
+// workgroup: three workgroups fit a CU, and the third wave hides more of the
+// VALU latency in that VALU-bound case).
+template <int DT, int D, bool CAUSAL, int MODE, bool PROBE, bool CMP>
+__global__ __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(2, (DT == DT_FP8 && D == 64) ? 3 : 2))) void
+attn_fwd_kernel(Params p) {
+  fwd_body<DT, D, CAUSAL, MODE, PROBE, CMP ? LAY_COMPACT : LAY_WIDE>(p);
+}
+
+// Bound by the chain of one wave's tiles rather than by the chip: a lone wave
+// on a SIMD takes about 4,000 cycles a tile at FP8 d = 128, a pair 2 tiles in
+// 5,500 (with both halves in step, 6,600).  4 heads of 8K, causal: FP8 118 ->
+// 95 us, BF16 144 -> 119; 16 heads of 2K: 34.5 -> 29.0, 41.6 -> 35.5.
+template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
+__global__ __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_paired_kernel(
+    Params p) {
+  fwd_body<DT, D, CAUSAL, MODE, PROBE, LAY_PAIRED>(p);
 }
 
 #if !H15_FP8_LATTICE_D128
@@ -905,14 +1011,21 @@ __global__ void probe_fill(float* s, float* w, uint32_t* pbits, size_t n) {
 template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
 hipError_t launch_one(const Params& p, hipStream_t st) {
   const unsigned grid = (unsigned)(p.nqb * p.B * p.Hq);
-  if constexpr (DT == DT_BF16 && MODE != MODE_ROWMAX_POT) {
-    if (p.compact) {
-      hipLaunchKernelGGL((attn_fwd_kernel<DT, D, CAUSAL, MODE, PROBE, true>), dim3(grid),
-                         dim3(Cfg<DT, D, true>::NW * 64), 0, st, p);
+  if constexpr (MODE != MODE_ROWMAX_POT) {
+    if (p.layout == LAY_PAIRED) {
+      hipLaunchKernelGGL((attn_fwd_paired_kernel<DT, D, CAUSAL, MODE, PROBE>), dim3(grid),
+                         dim3(Cfg<DT, D, LAY_PAIRED>::NW * 64), 0, st, p);
       return hipGetLastError();
     }
   }
-  if (p.compact) return hipErrorInvalidValue;  // offered for BF16 without Rowmax-PoT only
+  if constexpr (DT == DT_BF16 && MODE != MODE_ROWMAX_POT) {
+    if (p.layout == LAY_COMPACT) {
+      hipLaunchKernelGGL((attn_fwd_kernel<DT, D, CAUSAL, MODE, PROBE, true>), dim3(grid),
+                         dim3(Cfg<DT, D, LAY_COMPACT>::NW * 64), 0, st, p);
+      return hipGetLastError();
+    }
+  }
+  if (p.layout != LAY_WIDE) return hipErrorInvalidValue;  // not offered for this weight or type
   hipLaunchKernelGGL((attn_fwd_kernel<DT, D, CAUSAL, MODE, PROBE, false>), dim3(grid), dim3(Cfg<DT, D>::NW * 64), 0,
                      st, p);
   return hipGetLastError();

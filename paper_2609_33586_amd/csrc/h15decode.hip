@@ -63,15 +63,6 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("" ::: "memory");
 }
 
-// Barrier that makes this workgroup's LDS writes visible and leaves loads
-// from memory in flight (fences, also those of LDS alone, wait for the copies
-// into LDS).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // The scores are next read by inline asm (v_max3_f32, the masking's compare
 // and select), and the compiler inserts no wait states between a matrix-core
 // write and an inline-asm read: this holds the wave for 24, more than the 20
