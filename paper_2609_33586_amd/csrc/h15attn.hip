@@ -242,14 +242,17 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // offset inside the tile is the same for every tile, so it is computed
   // once; a tile then adds only the scalar offset of its first row.  Rows at
   // or beyond S (the ragged last tile) lie outside the resource's
-  // num_records = S * RB: the hardware range check (on the sum of both
-  // offsets, per dword) reads them as zero without touching memory, and
-  // those keys are masked.  The wave index is scalar, so the LDS
+  // num_records = S * RB: the hardware range check reads them as zero without
+  // touching memory, and those keys are masked.  The check compares the
+  // lane's offset with num_records minus the scalar offset, so the scalar one
+  // must not pass num_records (the difference would wrap): it is held there,
+  // where every lane is out of range.  The wave index is scalar, so the LDS
   // destinations (M0) are too.
   // (The addresses handed to the LDS-copy builtin are named variables: with
   // an arithmetic expression in those arguments the host side of this
   // compiler drops the kernels' launch stubs without a diagnostic.)
   constexpr int WAVE_LOADS = C::CHUNKS / (RW * 64);
+  const uint32_t head_bytes = (uint32_t)S * C::RB;
   const int wave_s = __builtin_amdgcn_readfirstlane(rw);
   // the chunk swizzles repeat every 16 rows, and a workgroup's 1 KB blocks
   // advance by a multiple of that, so one lane offset serves all loads
@@ -261,7 +264,7 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
     const uint32_t soff = (uint32_t)(t * BC) * C::RB;
 #pragma unroll
     for (int c = 0; c < WAVE_LOADS; ++c) {
-      const uint32_t so = soff + c * RW * 1024;
+      const uint32_t so = min(soff + c * RW * 1024, head_bytes);
       uint8_t* ldst = dst + (c * RW + wave_s) * 1024;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(void, ldst), 16, off, so, 0, 0);
     }

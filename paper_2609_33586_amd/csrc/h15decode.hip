@@ -277,7 +277,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- the part's K and V rows through buffer resources that hold just
   // them: rows beyond read as zero without touching memory (those keys are
   // masked), so every wave issues the same loads in every round and the
-  // waits can count them
+  // waits can count them.  The range check compares a lane's offset with the
+  // resource's size minus the scalar offset, so scalar offsets stop at the
+  // size (part_off), where every lane is out of range.
   const uint8_t* kg = p.k + ((size_t)bkv * (size_t)p.Sk_cap + (size_t)j0) * C::RB;
   const uint8_t* vg = p.v + ((size_t)bkv * (size_t)p.Sk_cap + (size_t)j0) * C::RB;
   const __amdgpu_buffer_rsrc_t krsrc =
@@ -285,6 +287,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const __amdgpu_buffer_rsrc_t vrsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)vg, (short)0, (j1 - j0) * C::RB, BUF_DWORD3);
 
+  const uint32_t part_bytes = (uint32_t)(j1 - j0) * C::RB;
+  auto part_off = [&](uint32_t byte) { return min(byte, part_bytes); };
   // this wave's first key of round c within the part
   const int wt = wave >> 1;  // tile of the round
   auto first_key = [&](int c) { return c * (TPR * BC) + wave * UNIT; };
@@ -307,7 +311,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (KLDS) {
 #pragma unroll
       for (int i = 0; i < LOADS; ++i) {
-        const uint32_t soff = (uint32_t)(first_key(c) * C::RB + i * 1024);
+        const uint32_t soff = part_off((uint32_t)first_key(c) * C::RB + i * 1024);
         const uint32_t voff = koff_c[i & 3];
         uint8_t* ldst = kslot + i * 1024;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(krsrc, LDS_PTR(void, ldst), 16, voff, soff, 0, 0);
@@ -317,7 +321,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const int krow = i32 * C::RB;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-      const int soff = (first_key(c) + 32 * kb) * C::RB;
+      const int soff = (int)part_off((uint32_t)(first_key(c) + 32 * kb) * C::RB);
 #pragma unroll
       for (int kk = 0; kk < NKQ; ++kk) {
         if constexpr (DT == DT_BF16) {
@@ -346,7 +350,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   auto stage_v = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const uint32_t soff = (uint32_t)(first_key(c) * C::RB + i * 1024);
+      const uint32_t soff = part_off((uint32_t)first_key(c) * C::RB + i * 1024);
       const uint32_t voff = voff_c[i & 1];
       uint8_t* ldst = vslot + i * 1024;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(vrsrc, LDS_PTR(void, ldst), 16, voff, soff, 0, 0);
