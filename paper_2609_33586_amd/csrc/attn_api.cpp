@@ -58,12 +58,14 @@ constexpr long long COMPACT_BELOW_GROUPS = 512;
 // five key tiles on (causal: four), below which its exchange at the end costs
 // what the shorter chain of tiles gains; and causal up to 512 blocks of long
 // rows, where the longest blocks decide when the call ends.  Paired against
-// the other layouts, time ratio at d = 128 (FP8 / BF16, causal unless said):
-// 128 blocks of 512 keys 1.05 / 1.12, 1K 1.10 / 1.19, 4K 1.19 / 1.29, all keys
-// visible 512 keys 1.02 / 1.08, 4K 1.19 / 1.30; 512 blocks of 1K keys 0.92 /
-// 0.96, 2K 1.05 / 1.05, 4K 1.12 / 1.13; 288 blocks of 512 keys 0.90 / 0.97, 2K
-// 1.16 / 1.11; 256 blocks of 256 keys 0.99 / 1.01; 288 blocks with all keys
-// visible 0.73; 600 blocks of 4K 0.91 / 0.88.
+// the other layouts, time ratio at d = 128 (FP8 / BF16, H15, causal unless
+// said): 128 blocks of 1K keys 1.26 / 1.20, 256 of 2K 1.34 / 1.26, 256 of 8K 1.47
+// / 1.31, 256 with all of 4K keys visible 1.26 / 1.17; 512 blocks of 4K 1.26 /
+// 1.11.  The lines were drawn with the first form of the layout, which the
+// later one only betters: 512 blocks of 1K keys 0.92 / 0.96, of 2K 1.05 / 1.05;
+// 288 blocks of 512 keys 0.90 / 0.97, of 2K 1.16 / 1.11; 256 blocks of 256 keys
+// 0.99 / 1.01; 288 blocks with all keys visible 0.73; 600 blocks of 4K 0.91 /
+// 0.88.
 bool use_paired(long long blocks, int S, int causal) {
   const int tiles = (S + BC - 1) / BC;
   if (blocks <= 256) return tiles >= (causal ? 4 : 5);

@@ -222,6 +222,16 @@ __device__ __forceinline__ void lds_wait(T& x) {
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N));
 }
 
+// s_waitcnt for vmcnt <= N only (gfx9 encoding: vmcnt in bits 3:0 and 15:14;
+// expcnt 6:4 and lgkmcnt 11:8 at their maxima, so not waited for)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+  asm volatile("" ::: "memory");
+}
+
 // Barrier that makes this workgroup's LDS writes visible and leaves loads
 // from memory in flight (fences, also those of LDS alone, wait for the copies
 // into LDS).

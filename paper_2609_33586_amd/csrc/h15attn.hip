@@ -186,14 +186,19 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // -0.7%, so the control keeps two buffers)
   constexpr int NSTAGE = (LAY == LAY_WIDE && DT == DT_FP8 && D == 128 && mode_lattice(MODE)) ? 1 : C::NSTAGE;
   static_assert(MODE != MODE_ROWMAX_POT || (NSTAGE == 2 && !PAIR), "the Rowmax-PoT first pass double-buffers K");
-  // paired: the tiles of each half of the waves; at the end the fp32 halves of
-  // O that the pairs exchange, then the bf16 rows
+  // Paired: one K and one V tile for each half of the waves; at the end they
+  // take the fp32 halves of O that the pairs exchange, then the bf16 rows,
+  // which have their own array where they do not fit behind.
   constexpr int NOB = D / 32 / C::NPAR;  // 32-column blocks of O that a wave writes
-  constexpr int OX = PAIR ? NW * NOB * 4096 : 0, OST = NW * WROWS * NOB * 64;
-  constexpr int TILES = C::NPAR * NSTAGE * C::BUF;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[TILES > OX + OST ? TILES : OX + OST];
-  // paired: each row's maximum in the last two tiles of either half; at the
-  // end the waves' anchors and row sums
+  constexpr int OX = NW * NOB * 4096 / 2, OST = NW * WROWS * NOB * 64;
+  constexpr bool OWN_OST = PAIR && 2 * C::TILE < OX + OST;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[PAIR ? 2 * C::TILE : NSTAGE * C::BUF];
+  __shared__ __attribute__((aligned(16))) uint8_t vsm[PAIR ? 2 * C::TILE : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t osm[OWN_OST ? OST : 16];
+  static_assert(!PAIR || 2 * C::TILE >= OX, "O exchange fits the tiles");
+  static_assert(PAIR || NSTAGE * C::BUF >= OST, "O staging fits the tiles");
+  // paired: each row's maximum in the last even and odd tile; at the end the
+  // waves' anchors and row sums
   __shared__ float mx_lds[2][2][PAIR ? BR : 1];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -210,7 +215,8 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // row wave; paired: parity of this wave's tiles
   const int rw = __builtin_amdgcn_readfirstlane(wave % RW);
   const int par = PAIR ? __builtin_amdgcn_readfirstlane(wave / RW) : 0;
-  uint8_t* const tiles = smem + par * C::BUF;
+  uint8_t* const ktile = smem + par * C::TILE;  // (single-buffered)
+  uint8_t* const vtile = PAIR ? vsm + par * C::TILE : smem + C::TILE;
   const int qw0 = q0 + rw * WROWS;
   const int qrow = qw0 + i32;
   const bool wave_live = qw0 < S;
@@ -237,7 +243,7 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // uses K buffer t % 2 and V buffer t % 2.
   const __amdgpu_buffer_rsrc_t krsrc = __builtin_amdgcn_make_buffer_rsrc((void*)kg, (short)0, S * C::RB, BUF_DWORD3);
   const __amdgpu_buffer_rsrc_t vrsrc = __builtin_amdgcn_make_buffer_rsrc((void*)vg, (short)0, S * C::RB, BUF_DWORD3);
-  auto kbuf = [&](int t) { return tiles + (t & 1) * C::BUF; };
+  auto kbuf = [&](int t) { return smem + (t & 1) * C::BUF; };
   // Each of the waves that share a tile copies its WAVE_LOADS 1 KB blocks.  The lane's byte
   // offset inside the tile is the same for every tile, so it is computed
   // once; a tile then adds only the scalar offset of its first row.  Rows at
@@ -254,21 +260,36 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   constexpr int WAVE_LOADS = C::CHUNKS / (RW * 64);
   const uint32_t head_bytes = (uint32_t)S * C::RB;
   const int wave_s = __builtin_amdgcn_readfirstlane(rw);
-  // the chunk swizzles repeat every 16 rows, and a workgroup's 1 KB blocks
-  // advance by a multiple of that, so one lane offset serves all loads
-  static_assert(RW * 64 / C::NCH % 16 == 0, "the swizzle repeats from load to load");
-  const int srow = (rw * 64 + lane) / C::NCH, spch = lane % C::NCH;
-  const uint32_t koff = (uint32_t)(srow * C::RB + ((spch ^ k_swz<DT, D>(srow)) << 4));
-  const uint32_t voff = (uint32_t)(srow * C::RB + ((spch ^ v_swz<DT, D>(srow)) << 4));
-  auto stage = [&](int t, uint8_t* dst, const __amdgpu_buffer_rsrc_t& rsrc, uint32_t off) __attribute__((always_inline)) {
-    const uint32_t soff = (uint32_t)(t * BC) * C::RB;
+  // Paired: the chunk swizzles repeat every 16 rows, and the 1 KB blocks
+  // advance by a multiple of that, so one lane offset serves all loads and the
+  // scalar offset moves; there the registers are short.  (In the other layouts
+  // the scalar instructions for that cost 0.5..1%.)
+  constexpr int LANE_OFFS = PAIR ? 1 : WAVE_LOADS;
+  static_assert(!PAIR || RW * 64 / C::NCH % 16 == 0, "the swizzle repeats from load to load");
+  uint32_t koff[LANE_OFFS], voff[LANE_OFFS];
+#pragma unroll
+  for (int c = 0; c < LANE_OFFS; ++c) {
+    const int slot = (c * RW + rw) * 64 + lane;
+    const int row = slot / C::NCH, pch = slot % C::NCH;
+    koff[c] = (uint32_t)(row * C::RB + ((pch ^ k_swz<DT, D>(row)) << 4));
+    voff[c] = (uint32_t)(row * C::RB + ((pch ^ v_swz<DT, D>(row)) << 4));
+  }
+  auto stage = [&](int t, uint8_t* dst, const __amdgpu_buffer_rsrc_t& rsrc,
+                   const uint32_t (&off)[LANE_OFFS]) __attribute__((always_inline)) {
+    // Paired: a tile beyond the last is out of the resource's range, so the
+    // copies are the same in every step and no branch hides them from the
+    // compiler's wait counting (with one, each first read of K waited for the
+    // copies of V)
+    const uint32_t soff = PAIR && t >= ntiles ? head_bytes : (uint32_t)(t * BC) * C::RB;
 #pragma unroll
     for (int c = 0; c < WAVE_LOADS; ++c) {
-      const uint32_t so = min(soff + c * RW * 1024, head_bytes);
+      const uint32_t so = PAIR ? min(soff + c * RW * 1024, head_bytes) : soff;
+      const uint32_t vo = off[PAIR ? 0 : c];
       uint8_t* ldst = dst + (c * RW + wave_s) * 1024;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(void, ldst), 16, off, so, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, LDS_PTR(void, ldst), 16, vo, so, 0, 0);
     }
   };
+
   // ---- Q through LDS: each wave copies its own 32 rows with the same
   // direct loads (16 contiguous bytes per lane, so each load covers whole
   // rows; rows at or beyond S read as zero), into a region the first K/V
@@ -279,14 +300,16 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // barrier after read_q).
   constexpr int QBYTES = WROWS * C::RB;
   constexpr int QREGION = NSTAGE == 1 ? C::TILE : C::BUF;
-  static_assert(QBYTES % 1024 == 0 && QREGION + RW * QBYTES <= NSTAGE * C::BUF, "Q staging layout");
+  static_assert(QBYTES % 2048 == 0, "Q staging layout");
+  static_assert(PAIR ? RW * QBYTES <= (OWN_OST ? OST : 2 * C::TILE) : QREGION + RW * QBYTES <= NSTAGE * C::BUF,
+                "Q staging layout");
   const __amdgpu_buffer_rsrc_t qrsrc =
       __builtin_amdgcn_make_buffer_rsrc((void*)(p.q + q_head * C::RB), (short)0, S * C::RB, BUF_DWORD3);
-  uint8_t* const qreg = smem + QREGION + wave_s * QBYTES;
+  uint8_t* const qreg = (OWN_OST ? osm : PAIR ? vsm : smem + QREGION) + wave_s * QBYTES;
   auto stage_q = [&]() __attribute__((always_inline)) {
-    if (par != 0) return;  // the other wave of the pair copies them
 #pragma unroll
-    for (int c = 0; c < QBYTES / 1024; ++c) {
+    for (int c0 = 0; c0 < QBYTES / 1024; c0 += C::NPAR) {
+      const int c = c0 + par;  // (paired: each of the two waves copies one half)
       const int slot = c * 64 + lane;
       const int row = slot / C::NCH, pch = slot % C::NCH;
       // (unsigned: rows past S may take the offset past 2^31, where the
@@ -337,6 +360,7 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // mode: the two halves in lch; lattice modes: eight dot2 chains in lch8,
   // one per word index, none longer than four)
   constexpr bool SPLIT = DT == DT_FP8 && MODE != MODE_ROWMAX_POT;
+  constexpr bool PACKED = mode_lattice(MODE);
   float lch[2];
   float lch8[8];
   float nb1_split = 0.0f;  // exact mode: the exponent bias of the open tile
@@ -612,7 +636,9 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
 
   // ---- the scores of tile t become weights, the running state moves, and P
   // is left in pb/pf for the PV product
-  auto softmax_tile = [&](int t, const uint8_t* vl, bool need_mask) __attribute__((always_inline)) {
+  // (softmax_exponents, then softmax_weights; V sits at vl)
+  float alpha = 1.0f;  // rescale factor of the open tile
+  auto softmax_exponents = [&](int t, const uint8_t* vl, bool need_mask) __attribute__((always_inline)) {
     const int kt0 = t * BC;
 
     // running maximum (threshold 0: moves to the maximum so far); Rowmax-PoT
@@ -620,7 +646,7 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
     float m_new = m_run;
     if constexpr (PAIR) {
       // the tile before, which the other wave of the pair has, then this one
-      const float mp = t > 0 ? mx_lds[1 - par][((t - 1) >> 1) & 1][rw * WROWS + i32] : -INFINITY;
+      const float mp = t > 0 ? mx_lds[0][1 - par][rw * WROWS + i32] : -INFINITY;
       m_new = next_anchor(m_run, mp, mp);
       m_new = next_anchor(m_new, m_tile, m_tile);
     } else if constexpr (MODE != MODE_ROWMAX_POT) {
@@ -628,13 +654,11 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
       with_partner(tile_max(sacc), ma, mb);
       m_new = next_anchor(m_run, ma, mb);
     }
-    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * p.c1);
+    alpha = __builtin_amdgcn_exp2f((m_run - m_new) * p.c1);
     m_run = m_new;
     // the first V^T operands of this tile load while the weights are computed
-    pv_begin(vl);
-
+    if constexpr (!PAIR) pv_begin(vl);
     // weights, in place over the scores (the lattice modes: as BF16 pairs)
-    constexpr bool PACKED = mode_lattice(MODE);
     if constexpr (PACKED) {
       const float nbk = __builtin_fmaf(-m_new, p.ck, (float)(1 << mode_order(MODE)) * off);
 #pragma unroll
@@ -658,6 +682,12 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
           mask_beyond(sacc, lim, __uint_as_float(sq_masked<MODE>()));
         }
       }
+    }
+  };
+  auto softmax_weights = [&](int t, const uint8_t* vl, bool need_mask) __attribute__((always_inline)) {
+    const int kt0 = t * BC;
+    if constexpr (PAIR) pv_begin(vl);
+    if constexpr (PACKED) {
 #pragma unroll
       for (int kb = 0; kb < (SPLIT ? 2 : 4); ++kb)
 #pragma unroll
@@ -676,13 +706,13 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-          for (int j = 0; j < 16; ++j) sacc[kb][j] = pot_weight(sacc[kb][j], m_new, p.c1);
+          for (int j = 0; j < 16; ++j) sacc[kb][j] = pot_weight(sacc[kb][j], m_run, p.c1);
         if (need_mask) {
           const int lim = (CAUSAL ? min(qrow, S - 1) : S - 1) - kt0 - 4 * g;
           mask_beyond(sacc, lim, 0.0f);
         }
       } else {
-        const float nb1 = __builtin_fmaf(-m_new, p.c1, off);
+        const float nb1 = __builtin_fmaf(-m_run, p.c1, off);
 #pragma unroll
         for (int kb = 0; kb < (SPLIT ? 2 : 4); ++kb)
 #pragma unroll
@@ -787,9 +817,10 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   // during the next QK^T; each wait for a copy comes just before the barrier
   // that makes it visible.
   // Paired: the waves of the odd tiles run one barrier behind those of the
-  // even ones, so of the two waves of a SIMD one is in its QK^T while the
-  // other computes weights and PV, and each tile's maximum is there when the
-  // next tile's anchor needs it.
+  // even ones, so of the two waves of a SIMD one is in the first half of its
+  // step (QK^T, maximum, anchor, exponents) while the other is in the second
+  // (weights, O rescale, PV), and each tile's maximum is there when the next
+  // tile's anchor needs it.
   auto scores = [&](const uint8_t* kl) __attribute__((always_inline)) {
     __builtin_amdgcn_s_setprio(1);
     qk(kl);
@@ -797,40 +828,51 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
     settle_scores(sacc);
   };
   auto weights_pv = [&](int t, const uint8_t* vl, bool need_mask) __attribute__((always_inline)) {
-    softmax_tile(t, vl, need_mask);
+    softmax_weights(t, vl, need_mask);
     __builtin_amdgcn_s_setprio(1);
     pv_finish();
     __builtin_amdgcn_s_setprio(0);
     if constexpr (SPLIT) probe_weights(t);
   };
+  // this wave's copy of V(t) has landed and its reads of K(t) are done
+  auto turn_k = [&](int t) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (PAIR || t + 1 < ntiles) stage(t + C::NPAR, ktile, krsrc, koff);
+  };
+  // this wave's copy of the next K has landed and its reads of V(t) are done
+  auto turn_v = [&](int t) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (PAIR || t + 1 < ntiles) stage(t + C::NPAR, vtile, vrsrc, voff);
+  };
   auto step_single = [&](int t) __attribute__((always_inline)) {
-    uint8_t* const kl = tiles;
-    bool need_mask = false;
-    if constexpr (PAIR) m_tile = -INFINITY;
+    if (t <= last_act) scores(ktile);
+    turn_k(t);
     if (t <= last_act) {
-      scores(kl);
-      if constexpr (PAIR) {
-        need_mask = finish_scores(t);
-        float ma, mb;
-        with_partner(tile_max(sacc), ma, mb);
-        m_tile = __builtin_fmaxf(ma, mb);
-      }
+      const bool need_mask = finish_scores(t);
+      softmax_exponents(t, vtile, need_mask);
+      weights_pv(t, vtile, need_mask);
     }
-    if constexpr (PAIR) {
-      if (g == 0) mx_lds[par][(t >> 1) & 1][rw * WROWS + i32] = m_tile;
+    turn_v(t);
+  };
+  auto step_paired = [&](int t, auto active) __attribute__((always_inline)) {
+    float* const mx = &mx_lds[0][par][rw * WROWS + i32];
+    if constexpr (decltype(active)::value) {
+      scores(ktile);
+      const bool need_mask = finish_scores(t);
+      float ma, mb;
+      with_partner(tile_max(sacc), ma, mb);
+      m_tile = __builtin_fmaxf(ma, mb);
+      if (g == 0) *mx = m_tile;
+      softmax_exponents(t, vtile, need_mask);
+      turn_k(t);
+      weights_pv(t, vtile, need_mask);
+    } else {
+      if (g == 0) *mx = -INFINITY;
+      turn_k(t);
     }
-    // this wave's copy of V(t) has landed and its reads of K(t) are done
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (t + C::NPAR < ntiles) stage(t + C::NPAR, kl, krsrc, koff);
-    if (t <= last_act) {
-      if constexpr (!PAIR) need_mask = finish_scores(t);
-      weights_pv(t, kl + C::TILE, need_mask);
-    }
-    // this wave's copy of the next K has landed and its reads of V(t) are done
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (t + C::NPAR < ntiles) stage(t + C::NPAR, kl + C::TILE, vrsrc, voff);
+    turn_v(t);
   };
   auto step = [&](int t, auto buf) __attribute__((always_inline)) {
     constexpr int P = decltype(buf)::value;
@@ -842,27 +884,48 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
     if (t <= last_act) {
       scores(kl);
       const bool need_mask = finish_scores(t);
+      softmax_exponents(t, kl + C::TILE, need_mask);
       weights_pv(t, kl + C::TILE, need_mask);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   };
-  if constexpr (NSTAGE == 1) {
+  if constexpr (PAIR) {
+    // Q where the rows of O go at the end, or in the V tiles
     stage_q();
-    if (par < ntiles) stage(par, tiles, krsrc, koff);
+    stage(par, ktile, krsrc, koff);
+    if constexpr (OWN_OST) {
+      __builtin_amdgcn_sched_barrier(0);
+      stage(par, vtile, vrsrc, voff);
+      // Q and K are there before the first step, V at its middle
+      wait_vmcnt<WAVE_LOADS>();
+      lds_barrier();
+      read_q();
+    } else {
+      wait_vmcnt<0>();
+      lds_barrier();
+      read_q();
+      lds_barrier();
+      stage(par, vtile, vrsrc, voff);
+    }
+    // (both halves cross the same number of barriers)
+    if (par != 0) lds_barrier();
+    int t = par;
+    for (; t <= last_act; t += 2) step_paired(t, std::true_type{});
+    for (; t < (ntiles + 1) / 2 * 2; t += 2) step_paired(t, std::false_type{});
+    if (par == 0) lds_barrier();
+    // (the last copies, of no tile, have landed before the tiles are reused)
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+  } else if constexpr (NSTAGE == 1) {
+    stage_q();
+    stage(0, ktile, krsrc, koff);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     read_q();
     __syncthreads();
-    if (par < ntiles) stage(par, tiles + C::TILE, vrsrc, voff);
-    if constexpr (PAIR) {
-      // both halves cross the same number of barriers
-      if (par != 0) lds_barrier();
-      for (int t = par; t < (ntiles + 1) / 2 * 2; t += 2) step_single(t);
-      if (par == 0) lds_barrier();
-    } else {
-      for (int t = 0; t < ntiles; ++t) step_single(t);
-    }
+    stage(0, vtile, vrsrc, voff);
+    for (int t = 0; t < ntiles; ++t) step_single(t);
   } else {
     if constexpr (MODE != MODE_ROWMAX_POT) stage_q();
     stage(0, smem, krsrc, koff);
@@ -884,23 +947,25 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
   float la, lb;
   with_partner(l_part, la, lb);
   float l = la + lb, m_end = m_run;
-  uint8_t* ost = smem + wave * (WROWS * NOB * 64);
+  uint8_t* const ost = (OWN_OST ? osm : PAIR ? smem + OX : smem) + wave * (WROWS * NOB * 64);
   if constexpr (PAIR) {
     // the two waves of a pair hold sums relative to their own anchors: each
     // sends the other its part of the other's columns through LDS, which is
     // free once every wave has passed the last barrier
-    f32x4* const ex = (f32x4*)smem;  // [wave][block][quarter][lane]
-    auto send = [&](auto other) __attribute__((always_inline)) {
+    // ([row wave][block][quarter][lane], the even half's in smem, the odd
+    // half's in vsm)
+    const int exo = rw * (NOB * 4 * 64) + lane;
+    auto send = [&](auto other, f32x4* ex) __attribute__((always_inline)) {
 #pragma unroll
       for (int o = 0; o < NOB; ++o)
 #pragma unroll
         for (int jq = 0; jq < 4; ++jq) {
           const f32x16& a = oacc[decltype(other)::value * NOB + o];
-          ex[((wave * NOB + o) * 4 + jq) * 64 + lane] = f32x4{a[4 * jq], a[4 * jq + 1], a[4 * jq + 2], a[4 * jq + 3]};
+          ex[exo + (o * 4 + jq) * 64] = f32x4{a[4 * jq], a[4 * jq + 1], a[4 * jq + 2], a[4 * jq + 3]};
         }
     };
-    if (par == 0) send(std::integral_constant<int, 1>{});
-    else send(std::integral_constant<int, 0>{});
+    if (par == 0) send(std::integral_constant<int, 1>{}, (f32x4*)smem);
+    else send(std::integral_constant<int, 0>{}, (f32x4*)vsm);
     if (g == 0) {
       mx_lds[0][par][rw * WROWS + i32] = m_run;
       mx_lds[1][par][rw * WROWS + i32] = l;
@@ -913,21 +978,19 @@ __device__ __forceinline__ void fwd_body(const Params& p) {
     const float fm = m_run == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_run - m_end) * p.c1);
     const float fo = m_other == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((m_other - m_end) * p.c1);
     l = fm * l + fo * mx_lds[1][1 - par][rw * WROWS + i32];
-    const int partner = wave ^ RW;
-    auto merge = [&](auto mine) __attribute__((always_inline)) {
+    auto merge = [&](auto half, const f32x4* ex) __attribute__((always_inline)) {
 #pragma unroll
       for (int o = 0; o < NOB; ++o)
 #pragma unroll
         for (int jq = 0; jq < 4; ++jq) {
-          const f32x4 x = ex[((partner * NOB + o) * 4 + jq) * 64 + lane];
+          const f32x4 x = ex[exo + (o * 4 + jq) * 64];
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            oacc[o][4 * jq + e] = fm * oacc[decltype(mine)::value * NOB + o][4 * jq + e] + fo * x[e];
+            oacc[o][4 * jq + e] = fm * oacc[decltype(half)::value * NOB + o][4 * jq + e] + fo * x[e];
         }
     };
-    if (par == 0) merge(std::integral_constant<int, 0>{});
-    else merge(std::integral_constant<int, 1>{});
-    ost += OX;
+    if (par == 0) merge(std::integral_constant<int, 0>{}, (const f32x4*)vsm);
+    else merge(std::integral_constant<int, 1>{}, (const f32x4*)smem);
   } else {
     if (!wave_live) return;
   }
@@ -991,8 +1054,10 @@ attn_fwd_kernel(Params p) {
 
 // Bound by the chain of one wave's tiles rather than by the chip: a lone wave
 // on a SIMD takes about 4,000 cycles a tile at FP8 d = 128, a pair 2 tiles in
-// 5,500 (with both halves in step, 6,600).  4 heads of 8K, causal: FP8 118 ->
-// 95 us, BF16 144 -> 119; 16 heads of 2K: 34.5 -> 29.0, 41.6 -> 35.5.
+// 5,300 (6,600 with both halves in step; 5,500 with the barrier right after
+// QK^T).  GPU time, causal: 4 heads of 8K FP8 H15 119 -> 81 us, BF16 144 ->
+// 110; 16 heads of 2K 34.6 -> 25.9, 41.6 -> 33.2; 16 heads of 1K 19.7 -> 15.7,
+// 23.8 -> 19.8.
 template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
 __global__ __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_paired_kernel(
     Params p) {

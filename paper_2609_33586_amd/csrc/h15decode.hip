@@ -53,16 +53,6 @@ constexpr int TPR = NW * UNIT / BC;  // tiles per round
 constexpr int SG_MFMA = 0x008;
 constexpr int SG_DS_READ = 0x100;
 
-// s_waitcnt for vmcnt <= N only (gfx9 encoding: vmcnt in bits 3:0 and 15:14;
-// expcnt 6:4 and lgkmcnt 11:8 at their maxima, so not waited for)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-  asm volatile("" ::: "memory");
-}
-
 // The scores are next read by inline asm (v_max3_f32, the masking's compare
 // and select), and the compiler inserts no wait states between a matrix-core
 // write and an inline-asm read: this holds the wave for 24, more than the 20
