@@ -87,27 +87,50 @@ def attn_tile_bc() -> int:
     return int(lib().attn_tile_bc())
 
 
+# Marshalling is on the path of every call, and the smallest calls are bound by
+# it (13 us a call, of which the kernel takes 6): types through one table, sizes
+# compared as they come, the stream as a raw handle.
+_types = None
+_raw_stream = None
+
+
+def _type_table():
+    """Operand type of each torch dtype."""
+    global _types
+    if _types is None:
+        import torch
+        _types = {torch.bfloat16: ATTN_BF16, torch.uint16: ATTN_BF16, torch.int16: ATTN_BF16,
+                  torch.float8_e4m3fn: ATTN_FP8_E4M3, torch.uint8: ATTN_FP8_E4M3}
+    return _types
+
+
 def _dtype_of(t) -> int:
-    import torch
-    if t.dtype in (torch.bfloat16, torch.uint16, torch.int16):
-        return ATTN_BF16
-    if t.dtype in (torch.float8_e4m3fn, torch.uint8):
-        return ATTN_FP8_E4M3
-    raise TypeError(f"unsupported operand dtype {t.dtype}")
+    dt = _type_table().get(t.dtype)
+    if dt is None:
+        raise TypeError(f"unsupported operand dtype {t.dtype}")
+    return dt
 
 
-def _check(q, k, v):
+def _check_tensors(q, k, v, what):
     for name, t in (("q", q), ("k", k), ("v", v)):
         if not t.is_cuda or not t.is_contiguous() or t.dim() != 4:
-            raise ValueError(f"{name} must be a contiguous 4-D device tensor [B,H,S,d]")
-    B, Hq, S, d = q.shape
-    Hkv = k.shape[1]
-    if tuple(k.shape) != (B, Hkv, S, d) or tuple(v.shape) != (B, Hkv, S, d):
-        raise ValueError("k and v must be [B,Hkv,S,d] with q's B, S, d")
+            raise ValueError(f"{name} must be a contiguous 4-D device tensor{what}")
+
+
+def _one_dtype(q, k, v) -> int:
     dt = _dtype_of(q)
     if _dtype_of(k) != dt or _dtype_of(v) != dt:
         raise TypeError("q, k, v must share one operand type")
-    return B, Hq, Hkv, S, d, dt
+    return dt
+
+
+def _check(q, k, v):
+    _check_tensors(q, k, v, " [B,H,S,d]")
+    B, Hq, S, d = q.shape
+    sk = k.shape
+    if sk != v.shape or sk[0] != B or sk[2] != S or sk[3] != d:
+        raise ValueError("k and v must be [B,Hkv,S,d] with q's B, S, d")
+    return B, Hq, sk[1], S, d, _one_dtype(q, k, v)
 
 
 def _outputs(q, out, lse, want_lse):
@@ -116,26 +139,38 @@ def _outputs(q, out, lse, want_lse):
     through the data pointers, so a given tensor must be contiguous, of the
     right shape and type, and on q's device."""
     import torch
-    B, Hq, S, d = q.shape
+    shape, device = q.shape, q.device
     if out is None:
-        out = torch.empty((B, Hq, S, d), dtype=torch.bfloat16, device=q.device)
-    elif (tuple(out.shape) != (B, Hq, S, d) or out.dtype != torch.bfloat16 or not out.is_contiguous()
-          or out.device != q.device):
-        raise ValueError(f"out must be a contiguous bfloat16 tensor {(B, Hq, S, d)} on {q.device}")
-    if lse is None and want_lse:
-        lse = torch.empty((B, Hq, S), dtype=torch.float32, device=q.device)
-    elif lse is not None and (tuple(lse.shape) != (B, Hq, S) or lse.dtype != torch.float32
-                              or not lse.is_contiguous() or lse.device != q.device):
-        raise ValueError(f"lse must be a contiguous float32 tensor {(B, Hq, S)} on {q.device}")
+        out = torch.empty(shape, dtype=torch.bfloat16, device=device)
+    elif out.shape != shape or out.dtype != torch.bfloat16 or not out.is_contiguous() or out.device != device:
+        raise ValueError(f"out must be a contiguous bfloat16 tensor {tuple(shape)} on {device}")
+    if lse is None:
+        if want_lse:
+            lse = torch.empty(shape[:3], dtype=torch.float32, device=device)
+    elif lse.shape != shape[:3] or lse.dtype != torch.float32 or not lse.is_contiguous() or lse.device != device:
+        raise ValueError(f"lse must be a contiguous float32 tensor {tuple(shape[:3])} on {device}")
     return out, lse
 
 
+def _current_stream() -> int:
+    """The handle of the current device's current stream (as
+    torch.cuda.current_stream().cuda_stream, without the stream object where
+    torch offers that)."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        try:
+            from torch._C import _cuda_getCurrentRawStream as raw, _cuda_getDevice as device
+            _raw_stream = lambda: raw(device())  # noqa: E731
+        except ImportError:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    return _raw_stream()
+
+
 def _opts(descale, stream, tau=0.0, tau_per_wave=False):
-    import torch
     qd, kd, vd = descale if descale is not None else (1.0, 1.0, 1.0)
-    st = stream if stream is not None else torch.cuda.current_stream()
-    return attn_opts(float(qd), float(kd), float(vd), ctypes.c_void_p(st.cuda_stream), float(tau),
-                     int(bool(tau_per_wave)))
+    return attn_opts(float(qd), float(kd), float(vd), stream.cuda_stream if stream is not None else _current_stream(),
+                     float(tau), int(bool(tau_per_wave)))
 
 
 def attn_fwd_ex(q, k, v, *, causal: bool, scale: float, exp_mode: int, descale=None, stream=None,
@@ -198,17 +233,13 @@ def attn_decode_workspace_bytes(B: int, Hq: int, Sq: int, Sk: int, d: int, split
 
 
 def _check_decode(q, k, v, Sk):
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if not t.is_cuda or not t.is_contiguous() or t.dim() != 4:
-            raise ValueError(f"{name} must be a contiguous 4-D device tensor")
+    _check_tensors(q, k, v, "")
     B, Hq, Sq, d = q.shape
-    Hkv, cap = k.shape[1], k.shape[2]
-    if tuple(k.shape) != (B, Hkv, cap, d) or tuple(v.shape) != tuple(k.shape):
+    sk = k.shape
+    cap = sk[2]
+    if sk != v.shape or sk[0] != B or sk[3] != d:
         raise ValueError("k and v must be [B,Hkv,Sk_cap,d] with q's B and d")
-    dt = _dtype_of(q)
-    if _dtype_of(k) != dt or _dtype_of(v) != dt:
-        raise TypeError("q, k, v must share one operand type")
-    return B, Hq, Hkv, Sq, (cap if Sk is None else int(Sk)), cap, d, dt
+    return B, Hq, sk[1], Sq, (cap if Sk is None else int(Sk)), cap, d, _one_dtype(q, k, v)
 
 
 def _workspace(q, B, Hq, Sq, Sk, d, split_keys, workspace):
