@@ -59,17 +59,15 @@ constexpr long long COMPACT_BELOW_GROUPS = 512;
 // what the shorter chain of tiles gains; and causal up to 512 blocks of long
 // rows, where the longest blocks decide when the call ends.  Paired against
 // the other layouts, time ratio at d = 128 (FP8 / BF16, H15, causal unless
-// said): 128 blocks of 1K keys 1.26 / 1.20, 256 of 2K 1.34 / 1.26, 256 of 8K 1.47
-// / 1.31, 256 with all of 4K keys visible 1.26 / 1.17; 512 blocks of 4K 1.26 /
-// 1.11.  The lines were drawn with the first form of the layout, which the
-// later one only betters: 512 blocks of 1K keys 0.92 / 0.96, of 2K 1.05 / 1.05;
-// 288 blocks of 512 keys 0.90 / 0.97, of 2K 1.16 / 1.11; 256 blocks of 256 keys
-// 0.99 / 1.01; 288 blocks with all keys visible 0.73; 600 blocks of 4K 0.91 /
-// 0.88.
+// said): 256 blocks of 256 keys 0.97 / 0.98, of 512 1.06 / 1.07, of 1K 1.18 /
+// 1.19, of 4K 1.38 / 1.33; 288 of 512 0.87 / 0.90; 320 of 1K 1.11 / 1.15; 384 of
+// 1K 1.03 / 1.03 (d = 64: 1.00 / 0.98), of 4K 1.43 / 1.29; 512 of 1K 0.96 / 0.99,
+// of 2K 1.13 / 1.13, of 4K 1.30 / 1.23; 608 of 4K 0.97 / 0.97; with all keys
+// visible 256 of 512 1.03 / 1.04, of 4K 1.28 / 1.16, 288 of 4K 0.80 / 0.79.
 bool use_paired(long long blocks, int S, int causal) {
   const int tiles = (S + BC - 1) / BC;
   if (blocks <= 256) return tiles >= (causal ? 4 : 5);
-  return causal && blocks <= 512 && S >= 4 * blocks;
+  return causal && blocks <= 512 && S >= (blocks <= 352 ? 1024 : 4 * blocks);
 }
 
 // The layout of a forward call (attn_device.h); Rowmax-PoT, whose first pass

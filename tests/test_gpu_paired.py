@@ -85,9 +85,11 @@ def test_paired_conditional_rescale(causal, per_wave):
 
 
 @pytest.mark.parametrize("Hq,Hkv,S,causal", [(64, 8, 512, True), (65, 5, 512, True), (32, 8, 2048, True),
-                                             (51, 3, 600, False), (52, 4, 600, False)])
+                                             (51, 3, 600, False), (52, 4, 600, False), (44, 4, 1024, True),
+                                             (45, 9, 1024, True)])
 def test_paired_rule_borders(Hq, Hkv, S, causal):
-    # 256 and 260 blocks, 512 blocks of 2048 rows, 255 and 260 with every key visible
+    # 256 and 260 blocks, 512 blocks of 2048 rows, 255 and 260 with every key
+    # visible, 352 and 360 blocks of 1024 rows
     for dt in (BF16, FP8):
         inp = synth.make_inputs(1, Hq, Hkv, S, 128, dt, sharp=True, seed=2600 + Hq)
         say(f"paired borders Hq={Hq} S={S} causal={causal} dtype={dt}")
