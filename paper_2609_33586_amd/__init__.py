@@ -1,6 +1,6 @@
 """Rowmax-H15 fused attention forward for MI355X (gfx950).
 
-A thin ctypes binding over ``libh15attn.so`` (built from ``csrc/h15attn.hip``
+A thin ctypes binding over ``libh15attn.so`` (built from ``csrc/``
 by ``build.py``).  Every step of the attention runs in the HIP kernels; this
 module only marshals torch tensors (device memory and streams) into the C ABI
 declared in ``include/h15attn.h``.  The functions carry the C names.

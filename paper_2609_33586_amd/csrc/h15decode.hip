@@ -5,8 +5,8 @@
 // tiles starting at the part's first key and the running maximum starting at
 // -inf; the parts' (m, l, O) then merge exactly.
 //
-// One workgroup = NW waves (4 or 8) for one (batch, KV head, block of 32
-// query rows, part).  The 32 rows are the G * Sq query rows of the KV head's
+// One workgroup = NW = 4 waves for one (batch, KV head, block of 32 query
+// rows, part).  The 32 rows are the G * Sq query rows of the KV head's
 // query heads (row r: head h = hkv G + r / Sq, position r % Sq), so the K/V
 // tiles are read once for all of them.
 //
@@ -24,7 +24,7 @@
 //     part's last one at the end;
 //   * no barrier waits for a copy: a wave loads only its own keys, K straight
 //     into its MFMA operand registers (the next round's as soon as this
-//     round's scores are computed) and V into its own LDS slots (the next
+//     round's scores are computed; or through LDS, see KLDS) and V into its own LDS slots (the next
 //     round's once this round's are read).  The barrier is a bare s_barrier
 //     after the wait for the LDS writes: the compiler's __syncthreads also
 //     waits for every load in flight, which serialised the copies with the
