@@ -152,7 +152,8 @@ int fill_params(Params& p, const void* q, const void* k, const void* v, void* o,
 // sequence, 1000 keys: 14.1 -> 12.8 us; 2 x 4 heads, 3000 keys: 18.6 -> 16.6).
 // Larger grids are bound by HBM and want two workgroups per CU (K in
 // registers against LDS: B16 8K 95.2 / 97.4 us, B64 4K 170.4 / 173.9, B200 1K
-// 146.1 / 151.0).  FP8 and d = 64 take LDS always: two workgroups fit.
+// 146.1 / 151.0).  FP8, d = 64 and units of 32 keys take LDS always: two
+// workgroups fit.
 constexpr long long DEC_KLDS_GROUPS = 256;
 
 
@@ -237,14 +238,30 @@ int bind_workspace(DecParams& p, int d, void* workspace, size_t workspace_bytes)
   return ATTN_OK;
 }
 
+// Keys of a wave and round.  With units of 64 keys a round of the four waves
+// covers two tiles, so a part of one tile leaves two waves without keys and
+// one of three tiles half of its second round: those take units of 32 keys, a
+// tile a round.  GPU time of one call with units of 64 -> 32 (32 heads over 8
+// KV heads, H15, causal): one tile, B1 6.3 -> 4.3 us, B200 27.9 -> 20.6, 512
+// full blocks of 32 rows 14.2 -> 11.3 (BF16), B200 19.6 -> 13.5 (FP8); three tiles, B1 8.4 -> 7.2,
+// B200 56.7 -> 51.6 (BF16), 30.2 -> 29.0 (FP8).  Two tiles: at BF16 d = 128,
+// whose units of 64 read K into registers on large grids, 6.2 -> 6.0 and 36.9 ->
+// 33.6; elsewhere one round of 64 is level or ahead (FP8 4.9 -> 5.1), and from
+// four tiles on the longer rounds are (B1 BF16 8.3 -> 8.3, FP8 6.1 -> 6.8).
+int decode_unit(const DecParams& p, int dtype, int d) {
+  const int tiles = p.split_keys / BC;
+  return (tiles == 1 || tiles == 3 || (tiles == 2 && dtype == ATTN_BF16 && d == 128)) ? 32 : 64;
+}
+
 // Whether K goes through LDS.
 int decode_k_lds(const DecParams& p, int dtype, int d) {
   const long long groups = (long long)p.B * p.Hkv * p.nrb * p.nsplit;
-  return (groups <= DEC_KLDS_GROUPS || dtype != ATTN_BF16 || d != 128) ? 1 : 0;
+  return (p.unit == 32 || groups <= DEC_KLDS_GROUPS || dtype != ATTN_BF16 || d != 128) ? 1 : 0;
 }
 
 int decode_launch(DecParams& p, int dtype, int d, int causal, int exp_mode, void* st, bool probe) {
   const int mode = kernel_mode(dtype, exp_mode, d, p.ck);
+  p.unit = decode_unit(p, dtype, d);
   p.k_lds = decode_k_lds(p, dtype, d);
   return launch_decode(p, dtype, d, causal, mode, st, probe) == 0 ? ATTN_OK : ATTN_ELAUNCH;
 }

@@ -63,7 +63,8 @@ struct DecParams {
   float* part_o;   // [rows][nsplit][d], unnormalised O of each part (nsplit > 1)
   float* part_ml;  // [rows][nsplit][2], (m, l) of each part (nsplit > 1)
   int B, Hq, Hkv, Sq, Sk, Sk_cap, G, R, nrb, nsplit, split_keys;
-  int k_lds;  // 1: K through LDS (0 only for BF16 at d = 128)
+  int unit;   // keys of a wave and round: 64, or 32 (parts of one to three tiles)
+  int k_lds;  // 1: K through LDS (0 only for BF16 at d = 128 and units of 64)
   float c1, ck, vd;
   // probe target (probe launches only): output row (pb, ph, pi)
   int pb, ph, pi;

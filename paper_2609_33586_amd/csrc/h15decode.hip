@@ -14,7 +14,9 @@
 // keys, by the chain of latencies from the first load to the last store.  The
 // split of the work shortens that chain and keeps many bytes in flight:
 //   * the unit of a wave is 64 keys, half a tile; a round covers NW / 2 whole
-//     tiles, so a part of n tiles takes ceil(2 n / NW) rounds;
+//     tiles, so a part of n tiles takes ceil(2 n / NW) rounds.  Parts of few
+//     tiles, where that would leave waves without keys, have units of 32
+//     keys and a tile a round (the rule: attn_api.cpp);
 //   * a weight is rounded relative to the running maximum at its own tile, the
 //     maximum over the tiles up to it, not to the last tile before it in some
 //     wave.  The waves therefore exchange the maxima of their 64 keys (one
@@ -47,8 +49,6 @@
 namespace {
 
 constexpr int NW = 4;               // waves per workgroup
-constexpr int UNIT = 64;            // keys of one wave and round
-constexpr int TPR = NW * UNIT / BC;  // tiles per round
 // instruction classes of __builtin_amdgcn_sched_group_barrier
 constexpr int SG_MFMA = 0x008;
 constexpr int SG_DS_READ = 0x100;
@@ -57,35 +57,46 @@ constexpr int SG_DS_READ = 0x100;
 // and select), and the compiler inserts no wait states between a matrix-core
 // write and an inline-asm read: this holds the wave for 24, more than the 20
 // that gfx950 requires after a 16-pass write.
-__device__ __forceinline__ void settle_scores2(f32x16 (&v)[2]) {
-  asm("s_nop 15\n\ts_nop 7" : "+v"(v[0]), "+v"(v[1]));
+template <int NB>
+__device__ __forceinline__ void settle_unit(f32x16 (&v)[NB]) {
+  if constexpr (NB == 2) asm("s_nop 15\n\ts_nop 7" : "+v"(v[0]), "+v"(v[1]));
+  else asm("s_nop 15\n\ts_nop 7" : "+v"(v[0]));
 }
 
-// y over the scores of 64 keys whose key offset lies beyond lim
-template <int E = 0>
-__device__ __forceinline__ void mask_beyond2(f32x16 (&v)[2], int lim, float y) {
-  if constexpr (E < 32) {
+// y over the scores of a unit (32 or 64 keys) whose key offset lies beyond lim
+template <int NB, int E = 0>
+__device__ __forceinline__ void mask_unit(f32x16 (&v)[NB], int lim, float y) {
+  if constexpr (E < 16 * NB) {
     constexpr int kb = E / 16, j = E % 16;
     v[kb][j] = select_beyond<kb * 32 + 8 * (j >> 2) + (j & 3)>(lim, v[kb][j], y);
-    mask_beyond2<E + 1>(v, lim, y);
+    mask_unit<NB, E + 1>(v, lim, y);
   }
 }
 
-__device__ __forceinline__ float unit_max(const f32x16 (&v)[2]) {
-  // 32 -> 11 -> 4 -> 2 -> 1
-  float a[11], b[4];
+template <int NB>
+__device__ __forceinline__ float unit_max(const f32x16 (&v)[NB]) {
+  // 32 -> 11 -> 4 -> 2 -> 1, or 16 -> 6 -> 2 -> 1
+  if constexpr (NB == 2) {
+    float a[11], b[4];
 #pragma unroll
-  for (int i = 0; i < 10; ++i) {
-    const int e0 = 3 * i, e1 = 3 * i + 1, e2 = 3 * i + 2;
-    a[i] = max3(v[e0 >> 4][e0 & 15], v[e1 >> 4][e1 & 15], v[e2 >> 4][e2 & 15]);
+    for (int i = 0; i < 10; ++i) {
+      const int e0 = 3 * i, e1 = 3 * i + 1, e2 = 3 * i + 2;
+      a[i] = max3(v[e0 >> 4][e0 & 15], v[e1 >> 4][e1 & 15], v[e2 >> 4][e2 & 15]);
+    }
+    a[10] = max3(v[1][14], v[1][15], v[1][15]);
+    b[0] = max3(a[0], a[1], a[2]);
+    b[1] = max3(a[3], a[4], a[5]);
+    b[2] = max3(a[6], a[7], a[8]);
+    b[3] = max3(a[9], a[10], a[10]);
+    const float c = max3(b[0], b[1], b[2]);
+    return max3(c, b[3], b[3]);
+  } else {
+    float a[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) a[i] = max3(v[0][3 * i], v[0][3 * i + 1], v[0][3 * i + 2]);
+    const float b0 = max3(a[0], a[1], a[2]), b1 = max3(a[3], a[4], v[0][15]);
+    return max3(b0, b1, b1);
   }
-  a[10] = max3(v[1][14], v[1][15], v[1][15]);
-  b[0] = max3(a[0], a[1], a[2]);
-  b[1] = max3(a[3], a[4], a[5]);
-  b[2] = max3(a[6], a[7], a[8]);
-  b[3] = max3(a[9], a[10], a[10]);
-  const float c = max3(b[0], b[1], b[2]);
-  return max3(c, b[3], b[3]);
 }
 
 // The transposing LDS reads of V operands, with their wait in the same
@@ -110,6 +121,19 @@ __device__ __forceinline__ void read_v16(i32x2v (&r)[16], uint32_t a0, uint32_t 
         "n"(56 * RB)
       : "memory");
 }
+// the four 8-row steps of 32 keys
+template <int RB>
+__device__ __forceinline__ void read_v16(i32x2v (&r)[8], uint32_t a0, uint32_t a1) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:%10\n\t"
+      "ds_read_b64_tr_b16 %2, %8 offset:%11\n\tds_read_b64_tr_b16 %3, %8 offset:%12\n\t"
+      "ds_read_b64_tr_b16 %4, %9\n\tds_read_b64_tr_b16 %5, %9 offset:%10\n\t"
+      "ds_read_b64_tr_b16 %6, %9 offset:%11\n\tds_read_b64_tr_b16 %7, %9 offset:%12\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
+      : "v"(a0), "v"(a1), "n"(8 * RB), "n"(16 * RB), "n"(24 * RB)
+      : "memory");
+}
 // fp8: two blocks of 32 columns, the four 16-row steps of 64 keys
 template <int RB>
 __device__ __forceinline__ void read_v8(i32x2v (&r)[8], uint32_t a0, uint32_t a1) {
@@ -121,6 +145,18 @@ __device__ __forceinline__ void read_v8(i32x2v (&r)[8], uint32_t a0, uint32_t a1
       "s_waitcnt lgkmcnt(0)"
       : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
       : "v"(a0), "v"(a1), "n"(16 * RB), "n"(32 * RB), "n"(48 * RB)
+      : "memory");
+}
+
+// the two 16-row steps of 32 keys
+template <int RB>
+__device__ __forceinline__ void read_v8(i32x2v (&r)[4], uint32_t a0, uint32_t a1) {
+  asm volatile(
+      "ds_read_b64_tr_b8 %0, %4\n\tds_read_b64_tr_b8 %1, %4 offset:%6\n\t"
+      "ds_read_b64_tr_b8 %2, %5\n\tds_read_b64_tr_b8 %3, %5 offset:%6\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3])
+      : "v"(a0), "v"(a1), "n"(16 * RB)
       : "memory");
 }
 
@@ -199,18 +235,27 @@ __device__ __forceinline__ void merge_row(const float* ml, const float* po, int 
   if (lse && lane == 0) *lse = 0.69314718055994531f * (m * c1 + log2f(l) - off);
 }
 
+// UNIT: keys of a wave and round.  ONE: the parts have one round, so there is
+// nothing to copy for a next one (one tile, B200, BF16: 22.4 -> 20.6 us; left
+// out of longer parts' last round by a branch, the rest of the loop schedules
+// worse: +2..25%).
 // KLDS: K of a round comes through LDS like V, in copies of whole rows, else
 // straight into the MFMA operand registers, in loads of 32 rows with 32 bytes
-// each.  The rule between them stands where it is applied (attn_api.cpp).
-template <int DT, int D, bool KLDS, bool CAUSAL, int MODE, bool PROBE>
+// each.  The rules between the forms stand where they are applied
+// (attn_api.cpp).
+template <int DT, int D, int UNIT, bool ONE, bool KLDS, bool CAUSAL, int MODE, bool PROBE>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_decode_kernel(DecParams p) {
   using C = Cfg<DT, D>;
   constexpr int NDB = D / 32;
   constexpr int NKQ = DT == DT_BF16 ? D / 16 : D / 64;
   constexpr int SLOT = UNIT * C::RB;                            // one wave's K or V rows of a round
   constexpr int LOADS = SLOT / 1024;                            // 1 KB LDS copies per wave and round
-  constexpr int KLOADS = KLDS ? LOADS : 2 * (DT == DT_BF16 ? NKQ : 2 * NKQ);  // K loads per lane and round
-  __shared__ __attribute__((aligned(16))) uint8_t vsm[NW * SLOT];
+  constexpr int NB = UNIT / 32;                                 // 32-key score blocks of a unit
+  constexpr int TPR = NW * UNIT / BC;                           // tiles per round
+  constexpr int KLOADS = KLDS ? LOADS : NB * (DT == DT_BF16 ? NKQ : 2 * NKQ);  // K loads per lane and round
+  static_assert(TPR == 1 || TPR == 2, "the anchors of a round");
+  constexpr int RROWS = 16;                                     // rows of a pass of the final reduction
+  __shared__ __attribute__((aligned(16))) uint8_t vsm[NW * (SLOT > RROWS * D * 4 ? SLOT : RROWS * D * 4)];
   // (an array of its own, so that the compiler tells the copies apart)
   __shared__ __attribute__((aligned(16))) uint8_t ksm[KLDS ? NW * SLOT : 16];
   __shared__ __attribute__((aligned(16))) float mx_lds[2][32][NW];
@@ -280,14 +325,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const uint32_t part_bytes = (uint32_t)(j1 - j0) * C::RB;
   auto part_off = [&](uint32_t byte) { return min(byte, part_bytes); };
   // this wave's first key of round c within the part
-  const int wt = wave >> 1;  // tile of the round
+  const int wt = TPR == 1 ? 0 : wave >> 1;  // tile of the round
   auto first_key = [&](int c) { return c * (TPR * BC) + wave * UNIT; };
 
   // K of this wave's 64 keys straight into the MFMA A operand (block kb, lane:
   // key 32 kb + i32; bf16: 16 bytes at 32 kk + 16 g of the row; fp8: 32 bytes
   // at 64 kk + 32 g)
   using KOp = std::conditional_t<DT == DT_BF16, bf16x8, i32x8>;
-  KOp kreg[2][NKQ];
+  KOp kreg[NB][NKQ];
   uint8_t* const kslot = ksm + (KLDS ? wave * SLOT : 0);
   const int kswz = k_swz<DT, D>(i32);  // == k_swz(32 kb + i32)
   // the chunk swizzle of K rows repeats after every fourth 1 KB copy
@@ -310,7 +355,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     }
     const int krow = i32 * C::RB;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
+    for (int kb = 0; kb < NB; ++kb) {
       const int soff = (int)part_off((uint32_t)(first_key(c) + 32 * kb) * C::RB);
 #pragma unroll
       for (int kk = 0; kk < NKQ; ++kk) {
@@ -388,15 +433,15 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (DT == DT_BF16) asm volatile("" : "+v"(qb16[kk]));
     else asm volatile("" : "+v"(qf8[kk]));
   }
-  const int nrounds = (ntiles + TPR - 1) / TPR;
+  const int nrounds = ONE ? 1 : (ntiles + TPR - 1) / TPR;
 #pragma unroll 1
   for (int c = 0; c < nrounds; ++c) {
     const int kw0 = j0 + first_key(c);  // first key of this wave's unit
     const bool need_mask = (CAUSAL && kw0 + UNIT - 1 > Sk - p.Sq) || (kw0 + UNIT > j1);
     const int lim = min(limit, j1 - 1) - kw0 - 4 * g;
 
-    // ---- S^T of this wave's 64 keys, and their maximum for each row
-    f32x16 sv[2];
+    // ---- S^T of this wave's keys, and their maximum for each row
+    f32x16 sv[NB];
     if constexpr (KLDS) {
       // this round's K copies have landed once at most the V copies issued
       // after them are outstanding
@@ -406,7 +451,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
     for (int kk = 0; kk < NKQ; ++kk)
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
+      for (int kb = 0; kb < NB; ++kb) {
         if constexpr (KLDS) {
           const uint8_t* kr = kslot + (32 * kb + i32) * C::RB;
           if constexpr (DT == DT_BF16) {
@@ -427,7 +472,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (KLDS) {
       // K operands are read four MFMAs ahead, and all of them before the next
       // copy goes into the slot
-      constexpr int RK = DT == DT_BF16 ? 1 : 2, NQK = 2 * NKQ, AHEAD = NQK < 4 ? NQK : 4;
+      constexpr int RK = DT == DT_BF16 ? 1 : 2, NQK = NB * NKQ, AHEAD = NQK < 4 ? NQK : 4;
       __builtin_amdgcn_sched_group_barrier(SG_DS_READ, RK * AHEAD, 0);
 #pragma unroll
       for (int i = 0; i < NQK; ++i) {
@@ -438,14 +483,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
     __builtin_amdgcn_sched_barrier(0);
-    load_k(c + 1);
-    settle_scores2(sv);
+    if constexpr (!ONE) load_k(c + 1);
+    settle_unit(sv);
     // keys beyond the row's limit or the cache
-    if (need_mask) mask_beyond2(sv, lim, -INFINITY);
+    if (need_mask) mask_unit(sv, lim, -INFINITY);
     if constexpr (PROBE) {
       if (probe_row) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int key = kw0 + 32 * kb + 8 * (j >> 2) + 4 * g + (j & 3);
@@ -466,7 +511,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       const f32x4 x = *(const f32x4*)mx;
       const float t0 = __builtin_fmaxf(x[0], x[1]), t1 = __builtin_fmaxf(x[2], x[3]);
       m_seen = max3(m_seen, t0, t1);
-      anchor = wt == 0 ? __builtin_fmaxf(anchor, t0) : m_seen;
+      anchor = TPR == 2 && wt == 0 ? __builtin_fmaxf(anchor, t0) : m_seen;
     }
     // a row that has seen no key yet keeps m = -inf, l = 0, O = 0
     const float alpha = anchor == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f((m_wave - anchor) * p.c1);
@@ -474,12 +519,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     m_wave = anchor;
 
     // ---- weights (in place), row sum
-    uint32_t wpk[2][8];
+    uint32_t wpk[NB][8];
     constexpr bool PACKED = mode_lattice(MODE);
     if constexpr (PACKED) {
       const float nbk = __builtin_fmaf(-m_use, p.ck, (float)(1 << mode_order(MODE)) * off);
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int j = 0; j < 16; ++j) sv[kb][j] = __uint_as_float(sq_pre<MODE>(sv[kb][j], p.ck, nbk));
       if (need_mask) {
@@ -487,16 +532,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
           // as the forward kernel: one max lifts exactly the masked keys
           const float lift = __uint_as_float(0x4B3F0000u | sq_masked<MODE>());
 #pragma unroll
-          for (int kb = 0; kb < 2; ++kb)
+          for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
             for (int j = 0; j < 16; ++j) sv[kb][j] = max3(sv[kb][j], lift, lift);
         } else {
-          mask_beyond2(sv, lim, __uint_as_float(sq_masked<MODE>()));
+          mask_unit(sv, lim, __uint_as_float(sq_masked<MODE>()));
         }
       }
       float a[4] = {l_part * alpha, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           wpk[kb][q] = sq_pack<MODE>(__float_as_uint(sv[kb][2 * q]), __float_as_uint(sv[kb][2 * q + 1]));
@@ -506,12 +551,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     } else {
       const float nb1 = __builtin_fmaf(-m_use, p.c1, off);
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int j = 0; j < 16; ++j) sv[kb][j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[kb][j], p.c1, nb1));
       float a[16];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) a[i] = sv[0][i] + sv[1][i];
+      for (int i = 0; i < 16; ++i) a[i] = NB == 2 ? sv[0][i] + sv[NB - 1][i] : sv[0][i];
 #pragma unroll
       for (int w = 8; w >= 1; w >>= 1)
 #pragma unroll
@@ -525,13 +570,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
         for (int j = 0; j < 16; ++j) oacc[db][j] *= alpha;
     }
 
-    // ---- P in the operand type: bf16 as four 16-key operands, fp8 as one
-    // 64-key operand
-    bf16x8 pb[4];
-    i32x8 pf;
+    // ---- P in the operand type: bf16 as 16-key operands, fp8 as one 64-key
+    // operand (a unit of 32 keys: P = 0 and V = 0 in its other half)
+    bf16x8 pb[2 * NB];
+    i32x8 pf = {0, 0, 0, 0, 0, 0, 0, 0};
     if constexpr (DT == DT_BF16) {
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
+      for (int ks = 0; ks < 2 * NB; ++ks) {
         const int kb = ks >> 1;
         if constexpr (PACKED) {
           const int q0 = 4 * (ks & 1);
@@ -544,7 +589,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       }
     } else {
 #pragma unroll
-      for (int w8 = 0; w8 < 8; ++w8) {
+      for (int w8 = 0; w8 < 4 * NB; ++w8) {
         const int kb = w8 >> 2, j4 = 4 * (w8 & 3);
         if constexpr (PACKED) {
           i16x2 word = __builtin_bit_cast(i16x2, wpk[kb][j4 / 2]);
@@ -564,7 +609,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     if constexpr (PROBE) {
       if (probe_row) {
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int key = kw0 + 32 * kb + 8 * (j >> 2) + 4 * g + (j & 3);
@@ -588,35 +633,37 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // once at most the next round's K loads, issued after it, are
     // outstanding (the probe's stores count too, so the probe waits for
     // all)
-    if constexpr (PROBE) wait_vmcnt<0>();
+    if constexpr (PROBE || ONE) wait_vmcnt<0>();
     else wait_vmcnt<KLOADS>();
 #pragma unroll
     for (int db = 0; db < NDB; db += 2) {
       if constexpr (DT == DT_BF16) {
-        i32x2v r[16];
+        i32x2v r[8 * NB];
         read_v16<C::RB>(r, vaddr[db], vaddr[db + 1]);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < 2 * NB; ++ks)
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
-            const bf16x8 vop = __builtin_bit_cast(
-                bf16x8, __builtin_shufflevector(r[8 * h + 2 * ks], r[8 * h + 2 * ks + 1], 0, 1, 2, 3));
+            const int r0 = 4 * NB * h + 2 * ks;
+            const bf16x8 vop = __builtin_bit_cast(bf16x8, __builtin_shufflevector(r[r0], r[r0 + 1], 0, 1, 2, 3));
             oacc[db + h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vop, pb[ks], oacc[db + h], 0, 0, 0);
           }
       } else {
-        i32x2v r[8];
+        i32x2v r[4 * NB];
         read_v8<C::RB>(r, vaddr[db], vaddr[db + 1]);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-          const i32x4 lo = __builtin_shufflevector(r[4 * h], r[4 * h + 1], 0, 1, 2, 3);
-          const i32x4 hi = __builtin_shufflevector(r[4 * h + 2], r[4 * h + 3], 0, 1, 2, 3);
+          const int r0 = 2 * NB * h;
+          const i32x4 lo = __builtin_shufflevector(r[r0], r[r0 + 1], 0, 1, 2, 3);
+          i32x4 hi = {0, 0, 0, 0};
+          if constexpr (NB == 2) hi = __builtin_shufflevector(r[r0 + 2], r[r0 + 3], 0, 1, 2, 3);
           const i32x8 vop = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
           oacc[db + h] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(vop, pf, oacc[db + h], 0, 0, 0, 0, 0, 0);
         }
       }
     }
     // (the slot has been read: the reads are waited for above)
-    stage_v(c + 1);
+    if constexpr (!ONE) stage_v(c + 1);
   }
   // every copy has landed (the last round's went to no key) and every wave is
   // done with its V slots before they are reused for the reduction
@@ -626,8 +673,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // ---- the waves' partial sums, each relative to its own anchor, added up
   // through LDS 16 rows at a time (chunks of four columns, XOR-swizzled by
   // row)
-  constexpr int RROWS = 16;
-  static_assert(NW * RROWS * D * 4 <= NW * SLOT, "the O reduction reuses the V slots");
   {
     float la, lb;
     with_partner(l_part, la, lb);
@@ -700,17 +745,24 @@ __global__ __launch_bounds__(256) void attn_decode_merge(MergeParams p) {
                p.off, p.o + (size_t)row * D, p.lse ? p.lse + row : nullptr);
 }
 
+template <int DT, int D, int UNIT, bool ONE, bool KLDS, bool CAUSAL, int MODE, bool PROBE>
+hipError_t launch_dec_kernel(const DecParams& p, hipStream_t st) {
+  const unsigned grid = (unsigned)(p.B * p.Hkv * p.nrb * p.nsplit);
+  hipLaunchKernelGGL((attn_decode_kernel<DT, D, UNIT, ONE, KLDS, CAUSAL, MODE, PROBE>), dim3(grid), dim3(NW * 64), 0,
+                     st, p);
+  return hipGetLastError();
+}
+
 template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
 hipError_t launch_dec_one(const DecParams& p, hipStream_t st) {
-  const unsigned grid = (unsigned)(p.B * p.Hkv * p.nrb * p.nsplit);
-  if constexpr (DT == DT_BF16 && D == 128) {
-    if (!p.k_lds) {
-      hipLaunchKernelGGL((attn_decode_kernel<DT, D, false, CAUSAL, MODE, PROBE>), dim3(grid), dim3(NW * 64), 0, st, p);
-      return hipGetLastError();
-    }
+  if (p.unit == 32) {
+    return p.split_keys == BC ? launch_dec_kernel<DT, D, 32, true, true, CAUSAL, MODE, PROBE>(p, st)
+                              : launch_dec_kernel<DT, D, 32, false, true, CAUSAL, MODE, PROBE>(p, st);
   }
-  hipLaunchKernelGGL((attn_decode_kernel<DT, D, true, CAUSAL, MODE, PROBE>), dim3(grid), dim3(NW * 64), 0, st, p);
-  return hipGetLastError();
+  if constexpr (DT == DT_BF16 && D == 128) {
+    if (!p.k_lds) return launch_dec_kernel<DT, D, 64, false, false, CAUSAL, MODE, PROBE>(p, st);
+  }
+  return launch_dec_kernel<DT, D, 64, false, true, CAUSAL, MODE, PROBE>(p, st);
 }
 
 template <int DT, int D, bool CAUSAL, bool PROBE>

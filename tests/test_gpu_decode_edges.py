@@ -14,7 +14,8 @@ import torch
 import oracle
 import paper_2609_33586_amd as pkg
 from paper_2609_33586_amd import synth
-from parity_helpers import BF16, EXACT, FP8, H15, ORACLE_MODE, TOL, assert_close, dev_tensors, say, scale_of, vmax
+from parity_helpers import (ALL_MODES, APPROX, BF16, EXACT, FP8, H15, ORACLE_MODE, TOL, assert_close, dev_tensors,
+                            say, scale_of, vmax)
 from test_gpu_decode import check_probe
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +48,40 @@ def test_decode_edges(B, Hq, Hkv, Sq, Sk, split, dt, d):
             assert np.max(np.abs(o - o_ref)) <= TOL[dt] * vmax(inp)
             assert bool(torch.isfinite(lse).all())
             check_probe(inp, Sk, True, scale_of(d), mode, split, ((0, 0, 0), (B - 1, Hq - 1, Sq - 1)))
+
+
+# parts of one to four tiles (units of 32 keys: one tile, three tiles and, at
+# BF16 d = 128, two), whole and ragged, one part and several
+SHORT = [(70, 0), (128, 0), (200, 0), (256, 0), (330, 0), (384, 0), (512, 0), (1000, 128), (900, 256), (1100, 384)]
+
+
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("dt,d", [(BF16, 128), (FP8, 128), (BF16, 64), (FP8, 64)])
+@pytest.mark.parametrize("Sk,split", SHORT)
+def test_decode_short_parts(Sk, split, dt, d, causal):
+    # 36 query rows of a KV head: a full block of rows and a ragged one, and
+    # rows that see no key of the last part.  Every weight's bits at two rows.
+    B, Hq, Hkv, Sq = 1, 24, 2, 3
+    inp = synth.make_decode_inputs(B, Hq, Hkv, Sq, Sk + 2, d, dt, sharp=True, seed=2900 + Sk)
+    q, k, v = dev_tensors(inp)
+    for mode in ALL_MODES:
+        say(f"decode short parts Sk={Sk} split={split} dtype={dt} d={d} causal={causal} mode={mode}")
+        o = torch.full((B, Hq, Sq, d), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        pkg.attn_decode(q, k, v, Sk=Sk, causal=causal, scale=scale_of(d), exp_mode=mode, split_keys=split,
+                        descale=inp.descale, out=o)
+        torch.cuda.synchronize()
+        o_ref, _ = oracle.decode(inp.q, inp.k, inp.v, Sk=Sk, dtype=dt, causal=causal, scale=scale_of(d),
+                                 mode=ORACLE_MODE[mode], split_keys=split, descale=inp.descale, Bc=128)
+        assert np.max(np.abs(o.float().cpu().numpy().astype(np.float64) - o_ref)) <= TOL[dt] * vmax(inp)
+        check_probe(inp, Sk, causal, scale_of(d), mode, split, ((0, 0, 0), (0, Hq - 1, Sq - 1)))
+
+
+@pytest.mark.parametrize("Sk,split", [(128, 0), (256, 0), (300, 0), (700, 384)])
+def test_decode_short_parts_float_clamp(Sk, split):
+    # FP8 with unit descales: the exponent bound passes 2^15, so the weights
+    # are clamped in FP32 (forms of their own at FP8)
+    rng = np.random.default_rng(2950)
+    x = [rng.integers(-3, 4, shape).astype(np.float32) for shape in ((1, 8, 2, 128), (1, 2, Sk, 128), (1, 2, Sk, 128))]
+    inp = synth.Inputs(*(synth.e4m3_codes(a) for a in x), (1.0, 1.0, 1.0), FP8)
+    for mode in APPROX:
+        check_probe(inp, Sk, True, scale_of(128), mode, split, ((0, 0, 0), (0, 7, 1)))
