@@ -243,7 +243,7 @@ int bind_workspace(DecParams& p, int d, void* workspace, size_t workspace_bytes)
 // one of three tiles half of its second round: those take units of 32 keys, a
 // tile a round.  GPU time of one call with units of 64 -> 32 (32 heads over 8
 // KV heads, H15, causal): one tile, B1 6.3 -> 4.3 us, B200 27.9 -> 20.6, 512
-// full blocks of 32 rows 14.2 -> 11.3 (BF16), B200 19.6 -> 13.5 (FP8); three tiles, B1 8.4 -> 7.2,
+// full blocks of 32 rows 14.2 -> 9.7 (BF16), B200 19.6 -> 13.5 (FP8); three tiles, B1 8.4 -> 7.2,
 // B200 56.7 -> 51.6 (BF16), 30.2 -> 29.0 (FP8).  Two tiles: at BF16 d = 128,
 // whose units of 64 read K into registers on large grids, 6.2 -> 6.0 and 36.9 ->
 // 33.6; elsewhere one round of 64 is level or ahead (FP8 4.9 -> 5.1), and from
