@@ -55,27 +55,48 @@ constexpr long long COMPACT_BELOW_GROUPS = 512;
 // The paired layout (8 waves for 128 rows, two waves a row) where there are
 // not enough blocks of 128 rows for two on every one of the 256 compute
 // units, so that a wave would have its SIMD to itself: up to 256 blocks, from
-// five key tiles on (causal: four), below which its exchange at the end costs
-// what the shorter chain of tiles gains; and causal up to 512 blocks of long
-// rows, where the longest blocks decide when the call ends.  Paired against
-// the other layouts, time ratio at d = 128 (FP8 / BF16, H15, causal unless
-// said): 256 blocks of 256 keys 0.97 / 0.98, of 512 1.06 / 1.07, of 1K 1.18 /
-// 1.19, of 4K 1.38 / 1.33; 288 of 512 0.87 / 0.90; 320 of 1K 1.11 / 1.15; 384 of
-// 1K 1.03 / 1.03 (d = 64: 1.00 / 0.98), of 4K 1.43 / 1.29; 512 of 1K 0.96 / 0.99,
-// of 2K 1.13 / 1.13, of 4K 1.30 / 1.23; 608 of 4K 0.97 / 0.97; with all keys
-// visible 256 of 512 1.03 / 1.04, of 4K 1.28 / 1.16, 288 of 4K 0.80 / 0.79.
-bool use_paired(long long blocks, int S, int causal) {
+// some number of key tiles on, below which its exchange at the end costs what
+// the shorter chain of tiles gains; and causal up to 512 blocks of long rows,
+// where the longest blocks decide when the call ends.
+//
+// Gain = time in the layout taken otherwise / time paired, over BF16 and FP8,
+// d = 64 and 128, H15 and exact (MHA, one box):
+//   causal, 256 blocks: 2 tiles 0.96..1.04, 3 tiles 0.97..1.05, 4 tiles
+//     1.06..1.10, 8 tiles 1.14..1.19, 16 tiles 1.19..1.28, 32 tiles 1.21..1.35;
+//   causal, S = 1024: 288 blocks of 512 rows 0.86..0.95, 320 blocks 1.08..1.16,
+//     352 blocks 1.03..1.12, 384 blocks 0.98..1.04, 400 blocks 0.95..1.00;
+//     S = 2048: 512 blocks 1.06..1.16; S = 1024: 512 blocks 0.90..0.98;
+//   all keys visible, 256 blocks: 2 tiles 0.90..0.95, 3 tiles 0.90..0.98,
+//     4 tiles 1.00..1.06 (d = 64 H15 1.00), 5 tiles 0.97..1.10, 8 tiles
+//     1.06..1.20, 32 tiles 1.14..1.28; 288 blocks of 4K rows 0.75..0.89.
+// A line stands where the forms gain clearly or on the whole; four tiles with all
+// keys visible and 384 blocks of 1K rows, level for some forms, stay out.
+// BF16 at d = 128 spends longer in the matrix core, which the two waves of a row
+// share: where the last, longest block has fewer than four live row waves
+// (its last row in the first 96 of 128), the other layout's chain is as short.
+// Causal, last row in the first 96 (60 and 256 blocks): lattice weights 4 tiles
+// 0.94..0.97, 5 0.96..1.00, 6 0.98..1.02, 7 0.98..1.05; exact 4 tiles 0.98..1.01, 5
+// 0.97..1.04, 6 1.01..1.06; last row beyond: 1.02..1.14 from 4 tiles on.  With all keys
+// visible and more than 240 blocks, exact at 5 tiles 0.93..1.00.
+bool use_paired(int dtype, int exp_mode, int d, long long blocks, int S, int causal) {
   const int tiles = (S + BC - 1) / BC;
-  if (blocks <= 256) return tiles >= (causal ? 4 : 5);
-  return causal && blocks <= 512 && S >= (blocks <= 352 ? 1024 : 4 * blocks);
+  if (blocks > 256) return causal && blocks <= 512 && S >= (blocks <= 352 ? 1024 : 4 * blocks);
+  int from = causal ? 4 : 5;
+  if (dtype == ATTN_BF16 && d == 128) {
+    const bool exact = exp_mode == ATTN_EXP_EXACT;
+    if (causal && (S - 1) % FWD_ROWS_SMALL < FWD_ROWS_SMALL - WROWS) from = exact ? 5 : 7;
+    if (!causal && exact && blocks > 240) from = 6;
+  }
+  return tiles >= from;
 }
 
 // The layout of a forward call (attn_device.h); Rowmax-PoT, whose first pass
 // double-buffers K, always takes the wide one.
-int fwd_layout(int dtype, int exp_mode, int B, int Hq, int S, int causal) {
+int fwd_layout(int dtype, int exp_mode, int B, int Hq, int S, int d, int causal) {
   if (exp_mode == ATTN_EXP_ROWMAX_POT) return LAY_WIDE;
   const long long heads = (long long)B * Hq;
-  if (use_paired(heads * ((S + FWD_ROWS_SMALL - 1) / FWD_ROWS_SMALL), S, causal)) return LAY_PAIRED;
+  const long long blocks = heads * ((S + FWD_ROWS_SMALL - 1) / FWD_ROWS_SMALL);
+  if (use_paired(dtype, exp_mode, d, blocks, S, causal)) return LAY_PAIRED;
   if (dtype != ATTN_BF16) return LAY_WIDE;
   const long long groups = heads * ((S + FWD_ROWS_BF16 - 1) / FWD_ROWS_BF16);
   return (S <= COMPACT_MAX_S || groups < COMPACT_BELOW_GROUPS) ? LAY_COMPACT : LAY_WIDE;
@@ -139,7 +160,7 @@ int fill_params(Params& p, const void* q, const void* k, const void* v, void* o,
   p.vd = vd;
   p.tau = tau;
   p.tau_wave = (opts && opts->rescale_per_wave) ? 1 : 0;
-  p.layout = fwd_layout(dtype, exp_mode, B, Hq, S, causal);
+  p.layout = fwd_layout(dtype, exp_mode, B, Hq, S, d, causal);
   p.nqb = (S + row_block(dtype, p.layout) - 1) / row_block(dtype, p.layout);
   p.remap = ((B * Hkv) % 8 == 0) ? 1 : 0;
   return ATTN_OK;

@@ -27,12 +27,20 @@ def host(tmp_path_factory):
                     str(lib)], check=True)
     L = ctypes.CDLL(str(lib))
     P, I, F, O = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.POINTER(pkg.attn_opts)
+    L.attn_fwd_ex.argtypes = [P] * 5 + [I] * 6 + [F, I, I, O]
     L.attn_decode.argtypes = [P] * 5 + [I] * 8 + [F, I, I, I, P, ctypes.c_size_t, O]
     return L
 
 
 def opts(tau=0.0):
     return ctypes.byref(pkg.attn_opts(1.0, 1.0, 1.0, None, tau, 0))
+
+
+def layout(L, dt, d, heads, S, causal, mode=pkg.ATTN_EXP_H15, tau=0.0):
+    a = ADDRESS
+    rc = L.attn_fwd_ex(a, a, a, a, None, 1, heads, heads, S, d, int(causal), 0.1, dt, mode, opts(tau))
+    assert rc == pkg.ATTN_ELAUNCH
+    return ("wide", "compact", "paired")[L.h15_stub_layout()]
 
 
 def decode_form(L, dt, d, B=1, Hq=8, Hkv=2, Sq=1, Sk=1000, split=0, mode=1):
@@ -67,3 +75,76 @@ def test_decode_k_path_by_workgroups(host, dt, d):
         assert B * Hkv * nrb * max(1, -(-sk // split) if split else 1) == groups
         want = 0 if groups > 256 and (dt, d) == (BF16, 128) else 1
         assert decode_form(host, dt, d, B=B, Hq=Hq, Hkv=Hkv, Sq=Sq, Sk=sk, split=split) == (64, want), (B, groups)
+
+
+EXACT, H15, SQ8, POT = pkg.ATTN_EXP_EXACT, pkg.ATTN_EXP_H15, pkg.ATTN_EXP_SQ8, pkg.ATTN_EXP_ROWMAX_POT
+
+
+def other(dt, S, heads):
+    """The layout of a call that is not paired."""
+    return "wide" if dt == FP8 or (S > 2048 and heads * -(-S // 256) >= 512) else "compact"
+
+
+@pytest.mark.parametrize("dt,d", DTD)
+def test_paired_from_some_tiles_on(host, dt, d):
+    # up to 256 blocks of 128 rows: causal from four tiles, else from five
+    for mode in (EXACT, H15, SQ8):
+        for S, causal, paired in ((128, True, False), (384, True, False), (481, True, True), (512, True, True),
+                                  (1024, True, True), (512, False, False), (513, False, True), (1024, False, True)):
+            want = "paired" if paired else other(dt, S, 4)
+            assert layout(host, dt, d, 4, S, causal, mode) == want, (S, causal, mode)
+    assert layout(host, dt, d, 4, 512, True, H15, tau=8.0 if dt == BF16 else 0.0) == "paired"
+
+
+def test_paired_ragged_last_block(host):
+    # BF16 d = 128, causal: a last block of 96 rows or fewer needs more tiles
+    for mode, tiles in ((EXACT, 5), (H15, 7), (SQ8, 7)):
+        for t in range(4, 10):
+            for r in (1, 64, 96):
+                want = "paired" if t >= tiles else "compact"
+                assert layout(host, BF16, 128, 4, (t - 1) * 128 + r, True, mode) == want, (mode, t, r)
+            for r in (97, 127, 128):
+                assert layout(host, BF16, 128, 4, (t - 1) * 128 + r, True, mode) == "paired", (mode, t, r)
+        for dt, d in ((FP8, 128), (BF16, 64), (FP8, 64)):
+            assert layout(host, dt, d, 4, 385, True, mode) == "paired"
+    # all keys visible: the exact control at five tiles, more than 240 blocks
+    assert layout(host, BF16, 128, 48, 600, False, EXACT) == "paired"
+    assert layout(host, BF16, 128, 49, 600, False, EXACT) == "compact"
+    assert layout(host, BF16, 128, 49, 600, False, H15) == "paired"
+    assert layout(host, BF16, 128, 41, 700, False, EXACT) == "paired"
+
+
+@pytest.mark.parametrize("dt,d", DTD)
+def test_layouts_by_blocks(host, dt, d):
+    # blocks of 128 rows: 256 and 257 (and one row more), the second line for
+    # long causal rows, and the compact layout's own lines
+    for heads, S, causal, paired in ((64, 512, True, True), (65, 512, True, False), (32, 1024, False, True),
+                                     (33, 1024, False, False), (44, 1024, True, True), (45, 1024, True, False),
+                                     (32, 2048, True, True), (33, 2048, True, False), (32, 2047, True, False),
+                                     (8, 8192, True, True), (9, 8192, True, False), (16, 4096, True, True),
+                                     (16, 4096, False, False), (1, 32768, False, True), (1, 32769, False, False)):
+        want = "paired" if paired else other(dt, S, heads)
+        assert layout(host, dt, d, heads, S, causal) == want, (heads, S, causal)
+    assert layout(host, dt, d, 64, 2048, True) == ("compact" if dt == BF16 else "wide")
+    assert layout(host, dt, d, 64, 2049, True) == "wide"
+    assert layout(host, dt, d, 31, 4096, True) == ("compact" if dt == BF16 else "wide")
+    assert layout(host, dt, d, 32, 4096, True) == "wide"
+    if dt == BF16:
+        for heads, S in ((1, 40), (4, 1024), (64, 4096)):
+            assert layout(host, dt, d, heads, S, True, POT) == "wide"
+
+
+def test_paired_test_shapes_are_paired(host):
+    # the shapes of test_gpu_paired.py, but for the ones it names
+    from test_gpu_paired import FULL
+    for dt, d in DTD:
+        for S, causal in FULL:
+            for mode in (EXACT, H15, SQ8):
+                small = (dt, d) == (BF16, 128) and (S == 385 or (S == 641 and mode != EXACT))
+                assert layout(host, dt, d, 2, S, causal, mode) == ("compact" if small else "paired"), (dt, d, S, mode)
+        for S in (520, 700, 900):
+            for causal in (True, False):
+                small = (dt, d) == (BF16, 128) and causal and S < 900
+                assert layout(host, dt, d, 2, S, causal) == ("compact" if small else "paired")
+                assert layout(host, dt, d, 64, S, causal) == other(dt, S, 64)
+        assert layout(host, dt, d, 4, 900, True) == layout(host, dt, d, 4, 900, False) == "paired"
