@@ -210,3 +210,13 @@ def test_library_links_both_kernel_units(L):
     assert len(lattice128) == 2 * 6 * 2  # causal x the six lattice modes x probe
     # BF16: d x causal x probe x (5 default + 4 compact); FP8: d x causal x probe x 7 modes
     assert len(stubs) == 2 * 2 * 2 * 9 + 2 * 2 * 2 * 7
+    # the paired layout: every weight but Rowmax-PoT, the FP8 lattice ones at
+    # d = 128 from the second compilation only
+    paired = re.findall(r"__device_stub__attn_fwd_paired_kernel<(\d), (\d+), (true|false), (\d), (true|false)>", out)
+    assert len(paired) == len(set(paired)) == 2 * 2 * 2 * 4 + 2 * 2 * 2 * 7
+    assert len({s for s in paired if s[0] == "1" and s[1] == "128" and s[3] != "0"}) == 2 * 6 * 2
+    # decode: types x d x causal x probe x modes, in units of 64 keys, of 32, and
+    # of 32 for one tile; BF16 d = 128 also with K in registers
+    dec = re.findall(r"__device_stub__attn_decode_kernel<(\d), (\d+), (32|64), (true|false), (true|false), "
+                     r"(true|false), (\d), (true|false)>", out)
+    assert len(dec) == len(set(dec)) == (3 * 2 + 1) * 4 * 4 + 3 * 2 * 4 * 7

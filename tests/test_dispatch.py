@@ -148,3 +148,30 @@ def test_paired_test_shapes_are_paired(host):
                 assert layout(host, dt, d, 2, S, causal) == ("compact" if small else "paired")
                 assert layout(host, dt, d, 64, S, causal) == other(dt, S, 64)
         assert layout(host, dt, d, 4, 900, True) == layout(host, dt, d, 4, 900, False) == "paired"
+
+
+def test_many_head_test_shapes(host):
+    # the shapes of test_gpu_layouts.py, test_gpu_tau.py and the write guards
+    import test_gpu_layouts as gl
+    import test_gpu_parity as gp
+    import test_gpu_tau as gt
+    for dt, hq, S, d in gl.MANY:
+        for causal in (True, False):
+            for mode in (EXACT, H15, SQ8):
+                want = "wide" if dt == FP8 or S == 2060 else "compact"
+                assert layout(host, dt, d, hq, S, causal, mode) == want, (dt, hq, S, d)
+    for dt, B, hq, hkv, S in gl.GROUPED:
+        assert B * hkv % 8 == 0
+        want = "wide" if dt == FP8 or S == 2100 else "compact"
+        assert layout(host, dt, 128, B * hq, S, True) == layout(host, dt, 128, B * hq, S, False) == want
+    for dt, hq, S in gl.LONG:
+        for mode in (EXACT, H15):
+            assert layout(host, dt, 128, hq, S, True, mode) == layout(host, dt, 128, hq, S, False, mode) == "paired"
+    for (hq, S, d), want in zip(gt.LAYOUTS, ("compact", "compact", "wide", "paired")):
+        for causal in (True, False):
+            assert layout(host, BF16, d, hq, S, causal, H15, tau=8.0) == want, (hq, S, d)
+    for dt, B, hq, hkv, S, d in gp.GUARD_SHAPES[-4:]:
+        for mode in (EXACT, H15):
+            assert layout(host, dt, d, B * hq, S, True, mode) == layout(host, dt, d, B * hq, S, False, mode) == "paired"
+    for B, hq, hkv, sq, sk, split in gl.REGISTER_K:
+        assert decode_form(host, BF16, 128, B=B, Hq=hq, Hkv=hkv, Sq=sq, Sk=sk, split=split) == (64, 0)

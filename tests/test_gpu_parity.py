@@ -307,6 +307,9 @@ def test_xcd_grouped_orders_write_every_row(dt):
 
 GUARD_SHAPES = [(BF16, 1, 4, 2, 333, 64), (BF16, 1, 4, 2, 333, 128), (FP8, 1, 4, 2, 333, 128),
                 (FP8, 2, 3, 3, 129, 64), (BF16, 1, 64, 8, 2500, 128)]  # the last: BF16's 8-wave layout
+# the paired layout: seven and nine tiles, one row and nine rows in the last block
+GUARD_SHAPES += [(BF16, 1, 4, 2, 777, 64), (BF16, 1, 4, 2, 777, 128), (FP8, 1, 4, 2, 777, 128),
+                 (FP8, 2, 3, 3, 1025, 64)]
 
 
 @pytest.mark.parametrize("dt,B,Hq,Hkv,S,d", GUARD_SHAPES)

@@ -60,20 +60,18 @@ def test_tau_full_parity(d, causal, S, mode, per_wave):
         assert np.any(o0 != o)
 
 
-@pytest.mark.parametrize("per_wave", [False, True])
-@pytest.mark.parametrize("mode", [H15, SQ4])
-@pytest.mark.parametrize("causal", [False, True])
-def test_tau_probe_bit_exact(causal, mode, per_wave):
-    S, d = 600, 128
-    inp = rising_inputs(S, d, Hq=2, Hkv=1, seed=701)
+def check_tau_probe(inp, causal, mode, per_wave, rowsets):
+    """Weights, P and LSE of sets (h, r0) of up to 32 rows (one wave's); how
+    often the shared decision moved the anchor and kept it."""
+    S, d = inp.q.shape[2], inp.q.shape[3]
     sc = scale_of(d)
     q, k, v = dev_tensors(inp)
     c1 = oracle.c1(sc)
     Bc = pkg.attn_tile_bc()
     moved = kept = 0
-    for (h, r0) in ((0, 0), (1, 256), (0, 544)):  # rows [r0, r0 + 32): one wave's rows
+    for (h, r0) in rowsets:
         n = min(32, S - r0)
-        say(f"tau probe causal={causal} mode={mode} per_wave={per_wave} head {h} rows {r0}+{n}")
+        say(f"tau probe S={S} causal={causal} mode={mode} per_wave={per_wave} head {h} rows {r0}+{n}")
         _, lse_p, s, w, pbits = pkg.attn_fwd_probe(q, k, v, causal=causal, scale=sc, exp_mode=mode, b=0, h=h,
                                                    row0=r0, nrows=n, tau=TAU, tau_per_wave=per_wave)
         torch.cuda.synchronize()
@@ -95,8 +93,35 @@ def test_tau_probe_bit_exact(causal, mode, per_wave):
             assert np.array_equal(w[r].view(np.uint32), w_ref.view(np.uint32)), f"row {i}"
             assert np.array_equal(pbits[r], p_ref), f"row {i}"
             assert abs(lse_p[0, h, i] - lse_ref) <= 1e-5, f"row {i}"
+    return moved, kept
+
+
+@pytest.mark.parametrize("per_wave", [False, True])
+@pytest.mark.parametrize("mode", [H15, SQ4])
+@pytest.mark.parametrize("causal", [False, True])
+def test_tau_probe_bit_exact(causal, mode, per_wave):
+    # two heads of 640 rows and fewer: the paired layout, or the compact one
+    # where the last block of a causal call is short
+    inp = rising_inputs(600, 128, Hq=2, Hkv=1, seed=701)
+    moved, kept = check_tau_probe(inp, causal, mode, per_wave, ((0, 0), (1, 256), (0, 544)))
     if per_wave and not causal:
         # both outcomes of the shared decision occur in these rows
+        assert moved > 0 and kept > 0
+
+
+# (query heads, S, d): the compact layout with five and six tiles (at d = 128
+# single-buffered), the wide one, and the paired one also when causal
+LAYOUTS = [(72, 610, 128), (72, 700, 64), (64, 2060, 128), (2, 640, 128)]
+
+
+@pytest.mark.parametrize("per_wave", [False, True])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Hq,S,d", LAYOUTS)
+def test_tau_probe_in_every_layout(Hq, S, d, causal, per_wave):
+    inp = rising_inputs(S, d, Hq=Hq, Hkv=2, seed=702)
+    r1 = (S - 1) // 32 * 32  # the last rows, fewer than 32 where S is ragged
+    moved, kept = check_tau_probe(inp, causal, H15, per_wave, ((Hq - 1, r1), (0, 288)))
+    if per_wave and not causal:
         assert moved > 0 and kept > 0
 
 
