@@ -315,16 +315,26 @@ def energy(seconds: float, workload: str):
           flush=True)
 
 
+# what the forward kernels are built from and chosen by
+FORWARD_SOURCES = ("csrc/h15attn.hip", "csrc/attn_device.h", "csrc/attn_params.h", "csrc/attn_api.cpp", "build.py")
+
+
+def forward_sources_sha() -> str:
+    import hashlib
+    sha = hashlib.sha256()
+    for name in FORWARD_SOURCES:
+        data = (ROOT / "paper_2609_33586_amd" / name).read_bytes()
+        sha.update(f"{name} {len(data)}\n".encode() + data)
+    return sha.hexdigest()[:16]
+
+
 def profiled_traffic(workload: str, mode: str):
     """HBM bytes per launch from the committed rocprofv3 counter summary, when it
-    was taken on the kernel source as it is now (else None)."""
-    import hashlib
+    was taken on the forward's sources as they are now (else None)."""
     path = ROOT / "profiles" / "hbm_traffic.txt"
-    src = ROOT / "paper_2609_33586_amd" / "csrc" / "h15attn.hip"
     try:
         rec = json.loads(path.read_text())
-        sha = hashlib.sha256(src.read_bytes()).hexdigest()[:16]
-        if rec.get("source_sha256_prefix") != sha:
+        if rec.get("source_sha256_prefix") != forward_sources_sha():
             return None
         t = rec["workloads"][workload][mode]
         return int(t["hbm_read_bytes"] + t["hbm_write_bytes"])

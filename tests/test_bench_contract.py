@@ -1,8 +1,9 @@
 """Host-side parts of the benchmark's contract (no GPU): the one-GPU refusal
 and the lookup of the profiled HBM traffic, which must report nothing once
-the kernel source differs from the one the counters were taken on."""
-import hashlib
+any source of the forward kernels differs from the ones the counters were
+taken on."""
 import json
+import re
 import shutil
 import subprocess
 import sys
@@ -26,9 +27,9 @@ def test_more_than_one_gpu_is_refused():
 @pytest.fixture
 def fake_root(tmp_path, monkeypatch):
     (tmp_path / "profiles").mkdir()
-    csrc = tmp_path / "paper_2609_33586_amd" / "csrc"
-    csrc.mkdir(parents=True)
-    shutil.copy(ROOT / "paper_2609_33586_amd" / "csrc" / "h15attn.hip", csrc / "h15attn.hip")
+    (tmp_path / "paper_2609_33586_amd" / "csrc").mkdir(parents=True)
+    for name in bench.FORWARD_SOURCES:
+        shutil.copy(ROOT / "paper_2609_33586_amd" / name, tmp_path / "paper_2609_33586_amd" / name)
     monkeypatch.setattr(bench, "ROOT", tmp_path)
     return tmp_path
 
@@ -40,18 +41,31 @@ def write_record(root, sha):
 
 
 def test_traffic_reported_for_the_profiled_source(fake_root):
-    src = fake_root / "paper_2609_33586_amd" / "csrc" / "h15attn.hip"
-    write_record(fake_root, hashlib.sha256(src.read_bytes()).hexdigest()[:16])
+    write_record(fake_root, bench.forward_sources_sha())
     assert bench.profiled_traffic("w", "h15") == 1234
     assert bench.profiled_traffic("w", "exact") is None
     assert bench.profiled_traffic("other", "h15") is None
 
 
-def test_traffic_null_once_the_source_changed(fake_root):
-    src = fake_root / "paper_2609_33586_amd" / "csrc" / "h15attn.hip"
-    write_record(fake_root, hashlib.sha256(src.read_bytes()).hexdigest()[:16])
+@pytest.mark.parametrize("name", ["csrc/h15attn.hip", "csrc/attn_device.h", "csrc/attn_params.h", "csrc/attn_api.cpp",
+                                  "build.py"])
+def test_traffic_null_once_a_source_changed(fake_root, name):
+    src = fake_root / "paper_2609_33586_amd" / name
+    write_record(fake_root, bench.forward_sources_sha())
     src.write_text(src.read_text() + "\n// edited\n")
     assert bench.profiled_traffic("w", "h15") is None
+
+
+def test_every_include_of_the_forward_kernels_is_hashed():
+    # the files that the kernel source pulls in from its own folder
+    csrc = ROOT / "paper_2609_33586_amd" / "csrc"
+    todo, seen = ["h15attn.hip"], set()
+    while todo:
+        name = todo.pop()
+        seen.add(name)
+        todo += [m for m in re.findall(r'#include "([^"]+)"', (csrc / name).read_text())
+                 if (csrc / m).exists() and m not in seen]
+    assert {f"csrc/{n}" for n in seen} <= set(bench.FORWARD_SOURCES)
 
 
 def test_committed_traffic_record_is_well_formed():
