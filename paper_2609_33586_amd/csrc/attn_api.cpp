@@ -2,7 +2,7 @@
 // constants of the method (the base-two logit scale c1 and its 2^k multiple,
 // App. B.1 "Implementation"; the offset of the FP8 weights), the choice of
 // kernel variant, the decode cut into key parts and its workspace, then the
-// launchers of h15attn.hip.  Plain C++: no HIP types or calls here, so the
+// launchers of h15attn.hip and h15decode.hip.  Plain C++: no HIP types or calls here, so the
 // same checks build with a host compiler alone under the sanitizers.
 #include <math.h>
 #include <stddef.h>
@@ -166,7 +166,6 @@ int fill_params(Params& p, const void* q, const void* k, const void* v, void* o,
   return ATTN_OK;
 }
 
-
 // Decode grids up to this many workgroups, one per compute unit, read K
 // through LDS also at BF16 d = 128, where that leaves room for only one
 // workgroup per CU: whole-row copies feed a CU faster than operand loads (one
@@ -176,7 +175,6 @@ int fill_params(Params& p, const void* q, const void* k, const void* v, void* o,
 // 146.1 / 151.0).  FP8, d = 64 and units of 32 keys take LDS always: two
 // workgroups fit.
 constexpr long long DEC_KLDS_GROUPS = 256;
-
 
 // Number of key parts for a cut of split_keys keys (0 or >= Sk: one part).
 int dec_parts(int Sk, int split_keys) {

@@ -1052,12 +1052,12 @@ attn_fwd_kernel(Params p) {
   fwd_body<DT, D, CAUSAL, MODE, PROBE, CMP ? LAY_COMPACT : LAY_WIDE>(p);
 }
 
-// Bound by the chain of one wave's tiles rather than by the chip: a lone wave
-// on a SIMD takes about 4,000 cycles a tile at FP8 d = 128, a pair 2 tiles in
-// 5,300 (6,600 with both halves in step; 5,500 with the barrier right after
-// QK^T).  GPU time, causal: 4 heads of 8K FP8 H15 119 -> 81 us, BF16 144 ->
-// 110; 16 heads of 2K 34.6 -> 25.9, 41.6 -> 33.2; 16 heads of 1K 19.7 -> 15.7,
-// 23.8 -> 19.8.
+// Bound by the chain of one wave's tiles rather than by the chip: from 4K to 8K
+// rows (FP8 H15, causal, 256 blocks) a tile of the longest chain costs 1.72 us
+// with a lone wave on each SIMD and 1.12 with two (about 4,000 and 2,600 cycles;
+// with both halves in step 3,300, with the barrier right after QK^T 2,750).  GPU
+// time, causal: 4 heads of 8K FP8 H15 119 -> 81 us, BF16 144 -> 110; 16 heads of
+// 2K 34.6 -> 25.9, 41.6 -> 33.2; 16 heads of 1K 19.7 -> 15.7, 23.8 -> 19.8.
 template <int DT, int D, bool CAUSAL, int MODE, bool PROBE>
 __global__ __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_paired_kernel(
     Params p) {

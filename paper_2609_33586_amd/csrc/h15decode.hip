@@ -163,10 +163,12 @@ __device__ __forceinline__ void read_v8(i32x2v (&r)[4], uint32_t a0, uint32_t a1
 // O and LSE of one row from its parts, by one wave: m = max m_p, f_p =
 // 2^(c1 (m_p - m)) (0 for a part that saw no key), l = sum f_p l_p,
 // O = sum f_p O_p / l * v_descale, LSE = ln2 (m c1 + log2 l - off).  Lane j
-// holds four columns and every (64 / (D / 4))th part, and up to 32 parts are
-// read at once, before their maximum is known, so that most rows cost one
-// round trip to memory: one wave reading its parts one after the other took
-// 11.8 us at 32 parts.
+// holds four columns and every (64 / (D / 4))th part, and the rows of up to 32
+// parts are in flight at once: 4.0 us at 32 parts and 32 rows, where one wave
+// reading its parts one after the other took 11.8.  As compiled a row still
+// costs two round trips, since the wait for its (m, l) comes before the first
+// row load, and, the row not being known to be uniform, each load's resource
+// goes through a loop over its values in the wave.
 template <int D>
 __device__ __forceinline__ void merge_row(const float* ml, const float* po, int nsplit, float c1, float vd, float off,
                                           uint16_t* orow, float* lse) {
