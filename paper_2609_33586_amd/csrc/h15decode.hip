@@ -712,8 +712,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
       f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int w = 0; w < NW; ++w) {
-        // (one tile a round: one anchor)
-        const float f = TPR == 1 ? 1.0f : mw[w] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f((mw[w] - m) * p.c1);
+        // (one tile a round: one anchor, and no exponential: 1, but NaN for an
+        // infinite anchor and 0 for a row without one, as the exponential has it)
+        const float fw = TPR == 1 ? 1.0f + (mw[w] - m) : __builtin_amdgcn_exp2f((mw[w] - m) * p.c1);
+        const float f = mw[w] == -INFINITY ? 0.0f : fw;
         l += f * lw[w];
         const f32x4 o = *(const f32x4*)(red + (w * RHALF + rr) * D + 4 * (ch ^ rr));
 #pragma unroll

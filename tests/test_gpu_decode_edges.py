@@ -85,3 +85,25 @@ def test_decode_short_parts_float_clamp(Sk, split):
     inp = synth.Inputs(*(synth.e4m3_codes(a) for a in x), (1.0, 1.0, 1.0), FP8)
     for mode in APPROX:
         check_probe(inp, Sk, True, scale_of(128), mode, split, ((0, 0, 0), (0, 7, 1)))
+
+
+@pytest.mark.parametrize("dt,d", [(BF16, 128), (FP8, 128), (BF16, 64), (FP8, 64)])
+@pytest.mark.parametrize("Sk,split", [(100, 0), (128, 0), (256, 0), (384, 0), (512, 0), (1100, 0), (1000, 128),
+                                      (1100, 384)])
+def test_decode_nan_query_gives_nan(Sk, split, dt, d):
+    # a query row that holds NaN has no score that compares: O is NaN in that row,
+    # in every form and weight, and every other row keeps its bits
+    inp = synth.make_decode_inputs(1, 8, 2, 3, Sk, d, dt, sharp=True, seed=2970 + Sk)
+    bad = np.array(inp.q)
+    bad[0, 5, 1] = 0x7FC0 if dt == BF16 else 0x7F
+    q, k, v = dev_tensors(inp)
+    qn = dev_tensors(synth.Inputs(bad, inp.k, inp.v, inp.descale, dt))[0]
+    for mode in ALL_MODES:
+        say(f"decode nan query Sk={Sk} split={split} dtype={dt} d={d} mode={mode}")
+        kw = dict(causal=True, scale=scale_of(d), exp_mode=mode, split_keys=split, descale=inp.descale)
+        o, lse = pkg.attn_decode(q, k, v, **kw)
+        on, ln = pkg.attn_decode(qn, k, v, **kw)
+        torch.cuda.synchronize()
+        assert bool(torch.isnan(on[0, 5, 1].float()).all()) and not bool(torch.isfinite(ln[0, 5, 1]))
+        on[0, 5, 1], ln[0, 5, 1] = o[0, 5, 1], lse[0, 5, 1]
+        assert torch.equal(on.view(torch.int16), o.view(torch.int16)) and torch.equal(ln, lse)
