@@ -19,7 +19,7 @@
 //     keys and a tile a round (the rule: attn_api.cpp);
 //   * a weight is rounded relative to the running maximum at its own tile, the
 //     maximum over the tiles up to it, not to the last tile before it in some
-//     wave.  The waves therefore exchange the maxima of their 64 keys (one
+//     wave.  The waves therefore exchange the maxima of their units (one
 //     barrier a round) and each takes the prefix maximum up to its tile as
 //     its anchor, which gives the recurrence's weights; row sums and O are
 //     kept per wave relative to the wave's own anchor and brought to the

@@ -1,7 +1,8 @@
 """Decode at the edges of its work split: a wave takes 64 keys a round and a
-workgroup of four waves two 128-key tiles, row blocks are grouped eight units
-(batch, KV head, part) at a time, the merge reads its parts 32 at a time, and
-BF16 at d = 128 reads K through LDS up to 256 workgroups.  O within 2e-2
+workgroup of four waves two 128-key tiles, or 32 keys and one tile in parts of
+one and three tiles (BF16 at d = 128 also of two), row blocks are grouped eight
+units (batch, KV head, part) at a time, the merge reads its parts 32 at a time,
+and BF16 at d = 128 reads K through LDS up to 256 workgroups.  O within 2e-2
 (BF16) or 6e-2 (FP8) max|V| of the oracle in every row; the exact control's
 LSE to 1e-3; H15's weights and P bit for bit, and its LSE to the fp32
 summation bound, against the oracle fed the GPU's logits (its LSE against the
